@@ -141,7 +141,7 @@ struct pp_ctx {
     Hier h64;                    // FP64 hierarchy (FP64 mode, and the mixed-mode fallback)
     double *pinv;
     int ncoarse;
-    double *hcoarse;             // pinned: the coarsest level's beta (3 arrays) and sigma, read back
+    double *pinv_work;           // elimination work of its rebuild (coarsest levels above one tile)
     double *hiter;               // pinned: the scalars of the last two outer iterations, read back
                                  // (HSLOT doubles each: the S_NSLOTS values, then a ticket)
     double ticket;               // the last ticket handed to a publishing kernel
@@ -152,18 +152,13 @@ struct pp_ctx {
                                  // r the V-cycle's scaled right-hand side)
     hipEvent_t iter_ev[2];       // their copies done
     hipEvent_t scal_ev;          // the scalar block's read-back (hscal) done
-    hipEvent_t coarse_ev;        // the coarsest coefficients' read-back (hcoarse) done
-    double *hpinv;               // pinned: the pseudo-inverse on its way to pinv
-    hipStream_t copy_stream;     // its upload, beside the stream's work ...
+    hipStream_t pinv_stream;     // the pseudo-inverse's rebuild, beside the stream's work ...
     hipEvent_t pinv_ev;          // ... done
-    hipEvent_t pinv_free;        // recorded where no V-cycle that reads pinv is still
-    bool pinv_free_set;          // queued after it: the upload need wait for nothing later
     hipStream_t aux_stream;      // pp_step's divergence and cold-start residual, beside the
     hipEvent_t aux_start;        // coefficient load: the stream's earlier work done (u*
     hipEvent_t aux_done;         // written) ... and that side-stream work done
-    bool pinv_wait;              // the next V-cycle waits for the upload before its coarse levels
-    bool pinv_dirty;             // the coefficients changed since pinv was built: the next
-                                 // V-cycle's caller builds it first (from hcoarse)
+    bool pinv_wait;              // the next V-cycle waits for the rebuild before its coarse levels
+    bool pinv_unchecked;         // its verdict (S_PINVBAD) has not been read yet
     bool check_pending;          // a density load's validity counts still to be read back
                                  // (by the next solve's first wait): pp_step
     bool scale_queued;           // the first V-cycle's scaled right-hand side is already queued
@@ -419,171 +414,6 @@ int fill_hier(pp_ctx *c, Hier &H, int from)
     return check_launch("convert coefficients");
 }
 
-// In place, lower triangle (row-major), right-looking: after column j is
-// scaled, every entry of the trailing lower triangle takes its update
-// independently (row by row over contiguous memory), so the loops carry no
-// chain of dependent additions.  The pseudo-inverse is rebuilt on the host
-// at every coefficient update, overlapping the GPU's work before the first
-// V-cycle needs it.
-int cholesky(std::vector<double> &a, int n)
-{
-    std::vector<double> col((size_t)n);
-    for (int j = 0; j < n; ++j) {
-        const double dgl = a[(size_t)j * n + j];
-        if (!(dgl > 0.0))
-            return -1;
-        const double d = std::sqrt(dgl);
-        a[(size_t)j * n + j] = d;
-        for (int i = j + 1; i < n; ++i) {
-            a[(size_t)i * n + j] /= d;
-            col[i] = a[(size_t)i * n + j];
-        }
-        for (int i = j + 1; i < n; ++i) {
-            const double lij = col[i];
-            double *ai = &a[(size_t)i * n];
-            for (int k = j + 1; k <= i; ++k)
-                ai[k] -= lij * col[k];
-        }
-    }
-    return 0;
-}
-
-// Enqueue the read-back of the coarsest level's coefficients into pinned
-// host memory; build_pinv waits for it (coarse_ev) before reading them.
-int enqueue_coarse_download(pp_ctx *c)
-{
-    const int L = c->nlev - 1;
-    const size_t n = cells(c->ld[L]);
-    const double *src[4] = {c->chain[L][0], c->chain[L][1], c->chain[L][2],
-                            c->sig_on ? c->sig[L] : nullptr};
-    launch_publish_arrays(src, c->sig_on ? 4 : 3, (int)n, c->hcoarse, c->stream);
-    PP_TRY(check_launch("coarsest coefficients read-back"));
-    PP_HIP(hipEventRecord(c->coarse_ev, c->stream));
-    return PP_OK;
-}
-
-// FP64 pseudo-inverse of the coarsest operator.  The pressure operator A is
-// singular (constants in the null space): with K = -A + (s/n) 1 1^T positive
-// definite, A^+ = (1/(s n)) 1 1^T - K^-1.  For the general operator
-// A - diag(sigma) the same is done on the active coarse cells (a nonzero
-// diagonal); when sigma is present the operator is definite there and
-// A^+ = -K^-1 with K = -A + diag(sigma).  Excluded cells get zero rows and
-// columns.
-// The coarsest coefficients come from the pinned read-back of
-// enqueue_coarse_download.
-int build_pinv(pp_ctx *c)
-{
-    const int L = c->nlev - 1;
-    const Dims d = c->ld[L];
-    const int n = (int)cells(d);
-    const double h = c->lh[L];
-    const double *b[3] = {c->hcoarse, c->hcoarse + n, c->hcoarse + 2 * (size_t)n};
-    const double *sg = c->sig_on ? c->hcoarse + 3 * (size_t)n : nullptr;
-    std::vector<double> A((size_t)n * n, 0.0);
-    const int nn[3] = {d.nx, d.ny, d.nz};
-    const int wall[3] = {c->bc.x, c->bc.y, c->bc.z};
-    for (int k = 0; k < d.nz; ++k)
-        for (int j = 0; j < d.ny; ++j)
-            for (int i = 0; i < d.nx; ++i) {
-                const int R = (k * d.ny + j) * d.nx + i;
-                int q[3] = {i, j, k};
-                for (int m = 0; m < 3; ++m) {
-                    int lo[3] = {q[0], q[1], q[2]};
-                    lo[m] -= 1;
-                    if (lo[m] < 0) {
-                        if (wall[m])
-                            continue;
-                        lo[m] += nn[m];
-                    }
-                    const int Lc = (lo[2] * d.ny + lo[1]) * d.nx + lo[0];
-                    const double w = b[m][R] / (h * h);
-                    A[(size_t)R * n + R] -= w;
-                    A[(size_t)R * n + Lc] += w;
-                    A[(size_t)Lc * n + Lc] -= w;
-                    A[(size_t)Lc * n + R] += w;
-                }
-                if (sg)
-                    A[(size_t)R * n + R] -= sg[R];
-            }
-    std::vector<int> idx;
-    for (int i = 0; i < n; ++i)
-        if (A[(size_t)i * n + i] < 0.0)
-            idx.push_back(i);
-    const int na = (int)idx.size();
-    if (na == 0)
-        return fail(PP_EINVAL, "coarsest operator is zero");
-    const bool singular = !c->gen || c->singular;
-    double s = 0.0;
-    for (int i = 0; i < na; ++i)
-        s = std::max(s, -A[(size_t)idx[i] * n + idx[i]]);
-    std::vector<double> K((size_t)na * na);
-    for (int i = 0; i < na; ++i)
-        for (int j = 0; j < na; ++j)
-            K[(size_t)i * na + j] = -A[(size_t)idx[i] * n + idx[j]] + (singular ? s / na : 0.0);
-    if (cholesky(K, na) != 0)
-        return fail(PP_EINVAL, "coarsest operator is not definite on mean-zero fields "
-                               "(disconnected domain?)");
-    // K^-1 = L^-T L^-1 = M^T M with M = L^-1, lower triangular.  M comes from
-    // L M = I by forward substitution, all columns at once: row i of M is
-    // (e_i - sum_{k<i} L_ik M_k) / L_ii over rows k already formed, each step
-    // an update of a contiguous row.  M^T M is summed as outer products of
-    // the rows of M.  No loop carries a chain of dependent additions.
-    std::vector<double> M((size_t)na * na, 0.0);
-    for (int i = 0; i < na; ++i) {
-        double *mi = &M[(size_t)i * na];
-        const double *li = &K[(size_t)i * na];
-        mi[i] = 1.0;
-        for (int k = 0; k < i; ++k) {
-            const double lik = li[k];
-            const double *mk = &M[(size_t)k * na];
-            for (int q = 0; q <= k; ++q)
-                mi[q] -= lik * mk[q];
-        }
-        const double inv = 1.0 / li[i];
-        for (int q = 0; q <= i; ++q)
-            mi[q] *= inv;
-    }
-    std::vector<double> G((size_t)na * na, 0.0);   // M^T M, lower triangle
-    for (int k = 0; k < na; ++k) {
-        const double *mk = &M[(size_t)k * na];
-        for (int a = 0; a <= k; ++a) {
-            const double mka = mk[a];
-            double *ga = &G[(size_t)a * na];
-            for (int bb = 0; bb <= a; ++bb)
-                ga[bb] += mka * mk[bb];
-        }
-    }
-    // the previous upload has read hpinv (it completed before that solve's
-    // coarse levels ran, so this returns at once)
-    PP_HIP(hipEventSynchronize(c->pinv_ev));
-    double *P = c->hpinv;
-    std::fill(P, P + (size_t)n * n, 0.0);
-    const double shift = singular ? 1.0 / (s * na) : 0.0;
-    for (int a = 0; a < na; ++a)
-        for (int bb = 0; bb <= a; ++bb) {
-            const double v = shift - G[(size_t)a * na + bb];
-            P[(size_t)idx[a] * n + idx[bb]] = v;
-            P[(size_t)idx[bb] * n + idx[a]] = v;
-        }
-    // The upload goes on a stream of its own, behind everything queued so far
-    // (no earlier coarsest solve can still read pinv), or only behind
-    // pinv_free where that was recorded, so the work the host queues next, up
-    // to the first coarse level, does not wait for the copy; that V-cycle
-    // waits for it before its coarse levels (pinv_wait)
-    if (c->pinv_free_set) {
-        PP_HIP(hipStreamWaitEvent(c->copy_stream, c->pinv_free, 0));
-        c->pinv_free_set = false;
-    } else {
-        PP_HIP(hipEventRecord(c->pinv_ev, c->stream));
-        PP_HIP(hipStreamWaitEvent(c->copy_stream, c->pinv_ev, 0));
-    }
-    PP_HIP(hipMemcpyAsync(c->pinv, P, sizeof(double) * n * n, hipMemcpyHostToDevice,
-                          c->copy_stream));
-    PP_HIP(hipEventRecord(c->pinv_ev, c->copy_stream));
-    c->pinv_wait = true;
-    return PP_OK;
-}
-
 // Wait until the kernel queued before `ev` has written `ticket` to *flag, in
 // pinned, coherent host memory, after the values it publishes.  Polling the
 // flag sees them as soon as the kernel has written them, before the end of the
@@ -633,18 +463,52 @@ int read_scal(pp_ctx *c)
 
 int nparts(pp_ctx *c) { return (int)grid_blocks(red_grid(c->d)); }
 
-// the coarsest level's pseudo-inverse for the current coefficients, built on
-// the host from the read-back coarsest coefficients and queued for upload
-int ensure_pinv(pp_ctx *c)
+// Rebuild the coarsest level's pseudo-inverse from the chain's coefficients
+// just queued, on a stream of its own: the first V-cycle waits for it before
+// its coarse levels (pinv_wait), so it overlaps the fine-level work queued
+// before them.  Every earlier V-cycle precedes the event it starts from.
+int queue_pinv(pp_ctx *c)
 {
-    if (!c->pinv_dirty)
-        return PP_OK;
-    // the read-back of the coarsest coefficients (a load that does not wait
-    // for its validity counts has not waited for it either)
-    PP_HIP(hipEventSynchronize(c->coarse_ev));
-    PP_TRY(build_pinv(c));
-    c->pinv_dirty = false;
+    const int L = c->nlev - 1;
+    PP_HIP(hipEventRecord(c->pinv_ev, c->stream));
+    PP_HIP(hipStreamWaitEvent(c->pinv_stream, c->pinv_ev, 0));
+    launch_pinv(c->ld[L], c->bc, c->lh[L], c->chain[L], c->sig_on ? c->sig[L] : nullptr,
+                !c->gen || c->singular, c->pinv_work, c->pinv, c->scal + S_PINVBAD,
+                c->pinv_stream);
+    PP_TRY(check_launch("coarsest pseudo-inverse"));
+    PP_HIP(hipEventRecord(c->pinv_ev, c->pinv_stream));
+    c->pinv_wait = true;
+    c->pinv_unchecked = true;
     return PP_OK;
+}
+
+// work queued on the stream from here on follows the pseudo-inverse's rebuild
+int await_pinv(pp_ctx *c)
+{
+    if (c->pinv_wait)
+        PP_HIP(hipStreamWaitEvent(c->stream, c->pinv_ev, 0));
+    c->pinv_wait = false;
+    return PP_OK;
+}
+
+// the verdict on the rebuilt pseudo-inverse, from scalars published behind it
+int pinv_verdict(pp_ctx *c, const double *scal)
+{
+    if (c->pinv_unchecked && scal[S_PINVBAD] != 0.0)
+        return fail(PP_EINVAL, "coarsest operator is not definite on mean-zero fields "
+                               "(disconnected domain?)");
+    c->pinv_unchecked = false;
+    return PP_OK;
+}
+
+// ... read back on its own where no V-cycle's scalars bring it
+int check_pinv(pp_ctx *c)
+{
+    if (!c->pinv_unchecked)
+        return PP_OK;
+    PP_TRY(await_pinv(c));
+    PP_TRY(read_scal(c));
+    return pinv_verdict(c, c->hscal);
 }
 
 // the prolongation weights of the levels from `from` on (all but the
@@ -664,6 +528,7 @@ int load_coeffs_general(pp_ctx *c, const double *bx, const double *by, const dou
                         const double *sg)
 {
     const double *src[3] = {bx, by, bz};
+    PP_TRY(await_pinv(c));   // a rebuild still reads the chain
     for (int m = 0; m < 3; ++m)
         PP_HIP(hipMemcpyAsync(c->chain[0][m], src[m], sizeof(double) * c->N, hipMemcpyDeviceToDevice,
                               c->stream));
@@ -703,14 +568,12 @@ int load_coeffs_general(pp_ctx *c, const double *bx, const double *by, const dou
                                    " entries are not finite non-negative numbers");
     PP_TRY(fill_hier(c, c->hmix, 0));
     PP_TRY(fill_hier(c, c->h64, 0));
-    PP_TRY(enqueue_coarse_download(c));
     PP_TRY(read_scal(c));
     c->singular = !(c->sig_on && c->hscal[S_SPOS] > 0.0);
     c->nact = c->hscal[S_NACT];
     if (!(c->nact > 0.0))
         return fail(PP_EINVAL, "no cell has an open face or a diagonal term");
-    c->pinv_dirty = true;
-    return PP_OK;
+    return queue_pinv(c);
 }
 
 // Level-0 coefficients into the FP64 chain (and the mixed hierarchy's level
@@ -742,6 +605,7 @@ int load_coeffs_impl(pp_ctx *c, const double *const src[3], const double *rho, b
     c->rho_ok = false;
     c->check_pending = false;
     c->b64_stale = false;
+    PP_TRY(await_pinv(c));   // a rebuild still reads the chain
     if (rho && !c->rho)
         PP_TRY(dev_alloc_t(c, &c->rho, sizeof(double) * c->N));
     int first_coarse = 0;   // first level whose coefficients are still to be coarsened from
@@ -847,10 +711,7 @@ int load_coeffs_impl(pp_ctx *c, const double *const src[3], const double *rho, b
     }
     PP_TRY(check_launch("coarsen coefficients"));
     PP_TRY(fill_hier(c, c->hmix, conv_from));
-    PP_TRY(enqueue_coarse_download(c));
-    // the coarsest pseudo-inverse is built on the host by the next solve,
-    // while the GPU works through what is queued before it
-    c->pinv_dirty = true;
+    PP_TRY(queue_pinv(c));
     c->rho_ok = rho != nullptr;
     if (defer) {
         c->check_pending = true;
@@ -1029,24 +890,13 @@ template <typename T>
 int vcycle_run(pp_ctx *c, Hier &H)
 {
     hipStream_t s = c->stream;
-    // a pseudo-inverse still to be built (pp_step leaves it to the first
-    // V-cycle, whose fine-level pass the GPU works on meanwhile) or an upload
-    // still on its way: the coarse levels wait for it
-    auto await_pinv = [c, s]() -> int {
-        PP_TRY(ensure_pinv(c));
-        if (c->pinv_wait) {
-            (void)hipStreamWaitEvent(s, c->pinv_ev, 0);
-            c->pinv_wait = false;
-        }
-        return PP_OK;
-    };
     if (H.tail == 0) {
-        PP_TRY(await_pinv());
+        PP_TRY(await_pinv(c));
         cycle_from<T>(c, H, 0, s);
         return PP_OK;
     }
     level_down<T>(c, H, 0, s);
-    PP_TRY(await_pinv());
+    PP_TRY(await_pinv(c));   // behind the fine-level pass: only the coarse levels need it
     if (!H.coarse_exec || hipGraphLaunch(H.coarse_exec, s) != hipSuccess)
         cycle_from<T>(c, H, 1, s);    // no graph, or it could not be launched: run eagerly
     level_up<T>(c, H, 0, s);
@@ -1196,27 +1046,12 @@ int true_residual(pp_ctx *c, const double *rhs, double *x, bool zero_x, SolveSta
     else if (pre)
         PP_TRY((*pre)());
     c->init_scaled = false;
-    // a pseudo-inverse still to be built is built here, on the host, while
-    // the GPU works through the residual and whatever was queued before it;
-    // its upload follows the read-back in the queue, unwaited.  After pp_step
-    // queued the residual early, the GPU has little left before it: the first
-    // V-cycle builds it instead, behind its first fine-level pass.
-    if (init_queued && c->pinv_dirty) {
-        // no V-cycle of this solve is queued yet, and every later one builds
-        // the pseudo-inverse before reading it: its upload may start from here
-        PP_HIP(hipEventRecord(c->pinv_free, c->stream));
-        c->pinv_free_set = true;
-    }
-    const int prc = init_queued ? PP_OK : ensure_pinv(c);
     PP_TRY(wait_scal(c));
     if (c->check_pending) {
-        // a deferred density check: its rejection takes precedence over a
-        // pseudo-inverse that failed on the rejected coefficients
+        // a deferred density check
         c->check_pending = false;
         PP_TRY(coeff_verdict(c, true, c->check_rho_count));
     }
-    if (prc != PP_OK)
-        return prc;
     S.nb = std::sqrt(c->hscal[S_BB]);
     S.rel = (S.nb > 0.0) ? std::sqrt(c->hscal[S_RR]) / S.nb : 0.0;
     return PP_OK;
@@ -1305,6 +1140,7 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
         PP_TRY(wait_ticket(c->hiter + slot * HSLOT + S_NSLOTS, c->iter_ticket[slot],
                            c->iter_ev[slot]));
         ++seen;
+        PP_TRY(pinv_verdict(c, c->hiter + slot * HSLOT));
         S.it++;
         const double before = S.rel;
         S.rel = std::sqrt(c->hiter[slot * HSLOT + S_RR]) / S.nb;
@@ -1386,6 +1222,7 @@ int dc_loop(pp_ctx *c, Hier &H, const double *rhs, double *x, double tol, SolveS
         launch_finalize(c->part, c->pstride, np, OP_DC, 0, (double)c->N, 0, c->scal, s);
         PP_TRY(check_launch("defect-correction iteration"));
         PP_TRY(read_scal(c));
+        PP_TRY(pinv_verdict(c, c->hscal));
         S.it++;
         S.rel = std::sqrt(c->hscal[S_RR]) / S.nb;
         record(S);
@@ -1537,6 +1374,8 @@ int solve_impl(pp_ctx *c, const double *rhs, double *x, double tol, pp_stats *st
             break;
         }
     }
+    if (S.it == 0)
+        PP_TRY(check_pinv(c));   // no iteration brought its verdict
     if ((rc == PP_OK || rc == PP_ENOCONV) && !gauged)
         PP_TRY(gauge(c, x));
     if (tail_queued)
@@ -1618,6 +1457,8 @@ void pp_destroy(pp_ctx *c)
     if (!c)
         return;
     (void)hipStreamSynchronize(c->stream);
+    if (c->pinv_stream)
+        (void)hipStreamSynchronize(c->pinv_stream);   // a rebuild no V-cycle waited for
     for (Hier *H : {&c->hmix, &c->h64})
         if (H->coarse_exec)
             (void)hipGraphExecDestroy(H->coarse_exec);
@@ -1629,10 +1470,6 @@ void pp_destroy(pp_ctx *c)
         (void)hipFree(p);
     if (c->hscal)
         (void)hipHostFree(c->hscal);
-    if (c->hcoarse)
-        (void)hipHostFree(c->hcoarse);
-    if (c->hpinv)
-        (void)hipHostFree(c->hpinv);
     if (c->hiter)
         (void)hipHostFree(c->hiter);
     for (hipEvent_t e : c->iter_ev)
@@ -1640,20 +1477,16 @@ void pp_destroy(pp_ctx *c)
             (void)hipEventDestroy(e);
     if (c->scal_ev)
         (void)hipEventDestroy(c->scal_ev);
-    if (c->coarse_ev)
-        (void)hipEventDestroy(c->coarse_ev);
     if (c->pinv_ev)
         (void)hipEventDestroy(c->pinv_ev);
-    if (c->copy_stream)
-        (void)hipStreamDestroy(c->copy_stream);
+    if (c->pinv_stream)
+        (void)hipStreamDestroy(c->pinv_stream);
     if (c->aux_start)
         (void)hipEventDestroy(c->aux_start);
     if (c->aux_done)
         (void)hipEventDestroy(c->aux_done);
     if (c->aux_stream)
         (void)hipStreamDestroy(c->aux_stream);
-    if (c->pinv_free)
-        (void)hipEventDestroy(c->pinv_free);
     delete c;
 }
 
@@ -1725,6 +1558,8 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->pinv, sizeof(double) * (size_t)c->ncoarse * c->ncoarse);
     if (rc == PP_OK)
+        rc = dev_alloc_t(c, &c->pinv_work, sizeof(double) * pinv_work_doubles(c->ncoarse));
+    if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->r64, sizeof(double) * c->N);
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->d64, sizeof(double) * c->N);
@@ -1742,16 +1577,6 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
     if (hipHostMalloc((void **)&c->hscal, sizeof(double) * HSLOT, hipHostMallocCoherent) !=
         hipSuccess) {
         c->hscal = nullptr;
-        return bail(fail(PP_ENOMEM, "hipHostMalloc failed"));
-    }
-    if (hipHostMalloc((void **)&c->hcoarse, sizeof(double) * 4 * (size_t)c->ncoarse,
-                      hipHostMallocCoherent) != hipSuccess) {
-        c->hcoarse = nullptr;
-        return bail(fail(PP_ENOMEM, "hipHostMalloc failed"));
-    }
-    if (hipHostMalloc((void **)&c->hpinv, sizeof(double) * (size_t)c->ncoarse * c->ncoarse,
-                      hipHostMallocDefault) != hipSuccess) {
-        c->hpinv = nullptr;
         return bail(fail(PP_ENOMEM, "hipHostMalloc failed"));
     }
     // coherent: the finalising kernel writes the iteration scalars here itself
@@ -1773,24 +1598,20 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
         c->scal_ev = nullptr;
         return bail(fail(PP_EHIP, "hipEventCreateWithFlags failed"));
     }
-    if (hipEventCreateWithFlags(&c->coarse_ev, hipEventDisableTiming) != hipSuccess) {
-        c->coarse_ev = nullptr;
-        return bail(fail(PP_EHIP, "hipEventCreateWithFlags failed"));
-    }
     if (hipEventCreateWithFlags(&c->pinv_ev, hipEventDisableTiming) != hipSuccess) {
         c->pinv_ev = nullptr;
         return bail(fail(PP_EHIP, "hipEventCreateWithFlags failed"));
     }
     // default priority, like every stream here
-    if (hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking) != hipSuccess) {
-        c->copy_stream = nullptr;
+    if (hipStreamCreateWithFlags(&c->pinv_stream, hipStreamNonBlocking) != hipSuccess) {
+        c->pinv_stream = nullptr;
         return bail(fail(PP_EHIP, "hipStreamCreateWithFlags failed"));
     }
     if (hipStreamCreateWithFlags(&c->aux_stream, hipStreamNonBlocking) != hipSuccess) {
         c->aux_stream = nullptr;
         return bail(fail(PP_EHIP, "hipStreamCreateWithFlags failed"));
     }
-    for (hipEvent_t *ev : {&c->aux_start, &c->aux_done, &c->pinv_free}) {
+    for (hipEvent_t *ev : {&c->aux_start, &c->aux_done}) {
         if (hipEventCreateWithFlags(ev, hipEventDisableTiming) != hipSuccess) {
             *ev = nullptr;
             return bail(fail(PP_EHIP, "hipEventCreateWithFlags failed"));
@@ -2360,7 +2181,7 @@ int pp_vcycle(pp_ctx *c, const double *r, double *e)
     PP_TRY(check_ctx(c));
     if (!r || !e)
         return fail(PP_EINVAL, "pp_vcycle: NULL array");
-    PP_TRY(ensure_pinv(c));
+    PP_TRY(check_pinv(c));
     Hier &H = (c->opts.precision == PP_FP64) ? c->h64 : c->hmix;
     LevelBuf &v0 = H.lev[0];
     switch (H.st) {

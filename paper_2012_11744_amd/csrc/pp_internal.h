@@ -109,7 +109,8 @@ enum Slot {
     S_NACT = 14,    // active cells of the general operator
     S_DS = 15,      // V-cycle scale of the latest direction (outer CG)
     S_APREV = 16,   // the previous outer iteration's ALPHA
-    S_NSLOTS = 17
+    S_PINVBAD = 17, // the coarsest pseudo-inverse met a pivot that is not a positive number
+    S_NSLOTS = 18
 };
 
 enum FinalizeOp {
@@ -171,8 +172,13 @@ void launch_prolong(Dims fd, Bc bc, const T *eH, T *e, const unsigned *w, hipStr
 // the prolongation weights of a level from its FP64 face coefficients
 void launch_prolong_weights(Dims d, Bc bc, const double *bx, const double *by, const double *bz,
                             unsigned *w, hipStream_t s);
-template <typename T>
-void launch_coarsest(int n, const double *pinv, const T *r, T *e, hipStream_t s);
+// the pseudo-inverse of the coarsest level's operator (n = cells(d) <= 1024)
+// from its FP64 coefficients and sigma (or null); singular: the constants on
+// the active cells are its null space; work: pinv_work_doubles(n) doubles;
+// *bad = 1 where the operator is not definite (off that null space), else 0
+size_t pinv_work_doubles(int n);
+void launch_pinv(Dims d, Bc bc, double h, const double *const b[3], const double *sg,
+                 bool singular, double *work, double *pinv, double *bad, hipStream_t s);
 // the V-cycle on nlev levels (the last one the coarsest) in one workgroup;
 // input r[0], output e[0] (in place; every level's e is overwritten); warm:
 // e[0] holds a correction on entry, which the first level's sweeps start from
@@ -249,9 +255,6 @@ void launch_fill(double *x, size_t n, double v, hipStream_t s);
 // block and quantity, quantity q at part[q * pstride + block]
 // act may be null (every cell); otherwise only active cells are summed
 void launch_sum(Dims d, const double *x, const unsigned char *act, double *part, hipStream_t s);
-// narr (at most 4) arrays of n doubles each, one after the other, to pinned,
-// coherent host memory, in one kernel
-void launch_publish_arrays(const double *const *src, int narr, int n, double *host, hipStream_t s);
 // n doubles to pinned, coherent host memory, written by a kernel; a nonzero
 // ticket is then written to host[n] (which must exist), after the values
 void launch_publish(const double *src, double *host, int n, hipStream_t s, double ticket = 0.0);

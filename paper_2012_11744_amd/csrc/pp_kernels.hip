@@ -509,23 +509,6 @@ __global__ __launch_bounds__(BLOCK) void k_prolong(Dims fd, Bc bc, const T *__re
     }
 }
 
-// Coarsest level: e = A^+ r with the FP64 pseudo-inverse (symmetric, n <= 1024).
-template <typename T>
-__global__ __launch_bounds__(1024) void k_coarsest(int n, const double *__restrict__ pinv,
-                                                   const T *__restrict__ r, T *__restrict__ e)
-{
-    __shared__ double rs[1024];
-    for (int t = threadIdx.x; t < n; t += blockDim.x)
-        rs[t] = static_cast<double>(r[t]);
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        double s = 0.0;
-        for (int jj = 0; jj < n; ++jj)
-            s += pinv[(size_t)jj * n + i] * rs[jj];
-        e[i] = static_cast<T>(s);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // The bottom of the V-cycle in one workgroup.  Levels of at most a few
 // thousand cells cost a kernel launch per step and little else, so all of
@@ -2618,15 +2601,6 @@ void launch_tail(int nlev, const Dims *d, const double *h2, const void *const (*
 }
 
 template <typename T>
-void launch_coarsest(int n, const double *pinv, const T *r, T *e, hipStream_t s)
-{
-    int threads = ((n + 63) / 64) * 64;
-    if (threads > 1024)
-        threads = 1024;
-    hipLaunchKernelGGL((k_coarsest<T>), dim3(1), dim3(threads), 0, s, n, pinv, r, e);
-}
-
-template <typename T>
 int launch_convert_scaled(size_t n, const double *src, double scale, double limit, T *dst,
                           double *part, int max_blocks, hipStream_t s)
 {
@@ -2805,28 +2779,6 @@ void launch_sum(Dims d, const double *x, const unsigned char *act, double *part,
     hipLaunchKernelGGL(k_sum, red_grid(d), kBlock, 0, s, d, x, act, part);
 }
 
-// up to four arrays of n doubles, one after the other into host
-struct PublishSrc {
-    const double *p[4];
-};
-
-__global__ __launch_bounds__(256) void k_publish_arrays(PublishSrc src, int narr, int n, double *host)
-{
-    for (int a = 0; a < narr; ++a)
-        for (int q = threadIdx.x; q < n; q += blockDim.x)
-            host[(size_t)a * n + q] = src.p[a][q];
-    __threadfence_system();
-}
-
-void launch_publish_arrays(const double *const *src, int narr, int n, double *host, hipStream_t s)
-{
-    PublishSrc ps{{nullptr, nullptr, nullptr, nullptr}};
-    for (int a = 0; a < narr && a < 4; ++a)
-        ps.p[a] = src[a];
-    hipLaunchKernelGGL(k_publish_arrays, dim3(1), dim3(256), 0, s, ps, narr < 4 ? narr : 4, n,
-                       host);
-}
-
 void launch_publish(const double *src, double *host, int n, hipStream_t s, double ticket)
 {
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, s, src, host, n, ticket);
@@ -2978,7 +2930,6 @@ void launch_sub_mean(size_t n, double *x, const double *scal, int slot, const un
     template int launch_load_density<T>(Dims, Bc, const double *, double *const[3], T *const[3], \
                                         double *const[3], double *, unsigned *, double *,       \
                                         hipStream_t);                                           \
-    template void launch_coarsest<T>(int, const double *, const T *, T *, hipStream_t);         \
     template void launch_tail<T>(int, const Dims *, const double *, const void *const (*)[3],   \
                                  void *const *, void *const *, const void *const *,             \
                                  const unsigned *const *, Bc, int, int, double, const double *, \
