@@ -141,6 +141,7 @@ struct pp_ctx {
     Hier h64;                    // FP64 hierarchy (FP64 mode, and the mixed-mode fallback)
     double *pinv;
     int ncoarse;
+    double *tail_state;          // what a split tail keeps between its launches
     double *pinv_work;           // elimination work of its rebuild (coarsest levels above one tile)
     double *hiter;               // pinned: the scalars of the last two outer iterations, read back
                                  // (HSLOT doubles each: the S_NSLOTS values, then a ticket)
@@ -850,7 +851,7 @@ void run_tail(pp_ctx *c, Hier &H, int t, hipStream_t s, bool warm = false)
         v.cur = v.e;
     }
     launch_tail<T>(n, d, h2, b, e, r, sg, w, c->bc, c->opts.nu_coarse, c->opts.nu_coarse,
-                   c->opts.omega, c->pinv, c->ncoarse, warm, s);
+                   c->opts.omega, c->pinv, c->ncoarse, warm, c->tail_state, s);
 }
 
 // The cycle on levels l .. L-1 for A e = r (input lev[l].r, output
@@ -1557,6 +1558,8 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
         rc = alloc_hier(c, c->hmix, o.precision == PP_MIXED_FP32 ? ST_F32 : ST_F16);
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->pinv, sizeof(double) * (size_t)c->ncoarse * c->ncoarse);
+    if (rc == PP_OK)
+        rc = dev_alloc_t(c, &c->tail_state, sizeof(double) * TAIL_STATE);
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->pinv_work, sizeof(double) * pinv_work_doubles(c->ncoarse));
     if (rc == PP_OK)

@@ -51,6 +51,7 @@ __host__ __device__ inline size_t cells(Dims d) { return (size_t)d.nx * d.ny * d
 // levels handled by the single-workgroup tail of the V-cycle
 constexpr int TAIL_MAX = 8;
 constexpr size_t TAIL_CELLS = 4096;       // a level joins the tail at or below this size
+constexpr int TAIL_STATE = 4096 + 2 * 512;   // doubles a split tail keeps between its launches
 constexpr size_t FUSED_MIN_CELLS = (size_t)1 << 18;   // fused sweeps above 64^3 cells
 // FP32 / FP16 storage, whose fused pass does two sweeps per launch, from 32^3 cells
 constexpr size_t FUSED2_MIN_CELLS = (size_t)1 << 14;
@@ -179,14 +180,16 @@ void launch_prolong_weights(Dims d, Bc bc, const double *bx, const double *by, c
 size_t pinv_work_doubles(int n);
 void launch_pinv(Dims d, Bc bc, double h, const double *const b[3], const double *sg,
                  bool singular, double *work, double *pinv, double *bad, hipStream_t s);
-// the V-cycle on nlev levels (the last one the coarsest) in one workgroup;
-// input r[0], output e[0] (in place; every level's e is overwritten); warm:
-// e[0] holds a correction on entry, which the first level's sweeps start from
+// the V-cycle on nlev levels (the last one the coarsest; at most 3, as a
+// smoothed level has even sides of at least 8 cells) in one workgroup, or, with
+// a large coarsest level, in one on the way down, many for its solve and one
+// on the way up; input r[0], output e[0]; warm: e[0] holds a correction on
+// entry, which the first level's sweeps start from; state: TAIL_STATE doubles
 template <typename T>
 void launch_tail(int nlev, const Dims *d, const double *h2, const void *const (*b)[3], void *const *e,
                  void *const *r, const void *const *sg, const unsigned *const *w, Bc bc,
                  int nu_pre, int nu_post, double omega, const double *pinv, int ncoarse,
-                 bool warm, hipStream_t s);
+                 bool warm, double *state, hipStream_t s);
 template <typename T>
 void launch_convert(size_t n, const double *src, T *dst, hipStream_t s);
 template <typename T>

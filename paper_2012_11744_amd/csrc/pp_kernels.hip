@@ -320,15 +320,6 @@ __global__ __launch_bounds__(BLOCK) void k_resid_restrict(Dims fd, Bc bc, const 
     }
 }
 
-__device__ __forceinline__ int other_parent(int i, int nH, int wall)
-{
-    const int I = i >> 1;
-    int o = (i & 1) ? I + 1 : I - 1;
-    if (o < 0 || o >= nH)
-        o = wall ? I : (o + nH) % nH;
-    return o;
-}
-
 // Weight of the far coarse cell in the prolongation of one fine cell along
 // one axis.  The fine cell lies between its parent's centre (at the face
 // between the two children) and the far coarse neighbour's centre (at the
@@ -507,387 +498,6 @@ __global__ __launch_bounds__(BLOCK) void k_prolong(Dims fd, Bc bc, const T *__re
             *ep = ev;
         }
     }
-}
-
-// ---------------------------------------------------------------------------
-// The bottom of the V-cycle in one workgroup.  Levels of at most a few
-// thousand cells cost a kernel launch per step and little else, so all of
-// them (smoothing, transfers and the coarsest solve) run in a single
-// 1024-thread workgroup that walks the levels with barriers between steps.
-// The arithmetic is the same as in the per-level kernels.
-// ---------------------------------------------------------------------------
-template <typename T>
-struct TailArgs {
-    int n;                     // levels in the tail (the last is the coarsest)
-    Dims d[TAIL_MAX];
-    double h2[TAIL_MAX];
-    const T *b[TAIL_MAX][3];
-    T *e[TAIL_MAX];
-    T *r[TAIL_MAX];
-    const T *s[TAIL_MAX];      // diagonal term of the general operator, or null
-    const unsigned *w[TAIL_MAX];   // prolongation weights of each level but the last, or null
-    Bc bc;
-    int nu_pre, nu_post;
-    double omega;              // the smoother's over-relaxation
-    const double *pinv;        // pseudo-inverse of the coarsest operator
-    int ncoarse;
-    int warm;                  // e[0] holds a correction to start the first level from
-};
-
-// Tail levels live in LDS: corrections and right-hand sides always, face
-// coefficients too when the arithmetic is FP32 (for FP64 they are read from
-// global memory, where they stay in L2).  Level q occupies cells
-// [off[q], off[q] + cells(d[q])) of each array.
-constexpr int TAIL_LDS = 4736;            // >= 4096 * (1 + 1/8 + 1/64 + ...)
-constexpr int TAIL_THREADS = 1024;
-constexpr int TAIL_PAIRS = 2;             // x-pairs per thread: 4096 cells / 2 / 1024
-constexpr int TAIL_PINV = 4096;           // coarsest pseudo-inverses of up to 64 cells are staged in LDS
-
-// One x-pair (cells i0, i0+1 of a row) of a smoothed tail level, as a thread
-// holds it during a visit of that level: LDS indices of the pair and of its
-// neighbours (level-relative, wraps resolved), the face coefficients with
-// walls zeroed, the right-hand side and the diagonal.
-template <typename C>
-struct TPair {
-    int c;                     // first cell
-    int xm, xp;                // the cell left of the pair, the cell right of it
-    int ym, yp, zm, zp;        // offsets of the y and z neighbours (the same for both cells)
-    int par;                   // colour of the first cell: (j + k) & 1
-    bool on;
-    C fx0, fx1, fx2;           // x faces: low of cell 0, between the cells, high of cell 1
-    C fyl[2], fyh[2], fzl[2], fzh[2];
-    C r[2], sg[2];
-    C dg[2];                   // sum of the face coefficients + h^2 sigma
-};
-
-template <typename C, typename TB, typename TS>
-__device__ __forceinline__ void tp_load(TPair<C> &P, Dims d, Bc bc, int p, const TB *bx,
-                                        const TB *by, const TB *bz, const C *R, const TS *sg,
-                                        C h2)
-{
-    const int hx = d.nx / 2;
-    const int npairs = hx * d.ny * d.nz;
-    P.on = p < npairs;
-    if (!P.on)
-        p = 0;
-    const int k = p / (hx * d.ny);
-    const int rem = p - k * hx * d.ny;
-    const int j = rem / hx;
-    const int i0 = 2 * (rem - j * hx);
-    const int nxy = d.nx * d.ny;
-    const int c = (k * d.ny + j) * d.nx + i0;
-    P.c = c;
-    P.par = (j + k) & 1;
-    P.xm = i0 == 0 ? c + d.nx - 1 : c - 1;
-    P.xp = i0 + 2 == d.nx ? c + 2 - d.nx : c + 2;
-    P.ym = j == 0 ? (d.ny - 1) * d.nx : -d.nx;
-    P.yp = j == d.ny - 1 ? -(d.ny - 1) * d.nx : d.nx;
-    P.zm = k == 0 ? (d.nz - 1) * nxy : -nxy;
-    P.zp = k == d.nz - 1 ? -(d.nz - 1) * nxy : nxy;
-    const bool wxl = bc.x && i0 == 0, wxh = bc.x && i0 + 2 == d.nx;
-    const bool wyl = bc.y && j == 0, wyh = bc.y && j == d.ny - 1;
-    const bool wzl = bc.z && k == 0, wzh = bc.z && k == d.nz - 1;
-    P.fx0 = wxl ? C(0) : C(bx[c]);
-    P.fx1 = C(bx[c + 1]);
-    P.fx2 = wxh ? C(0) : C(bx[P.xp]);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        P.fyl[q] = wyl ? C(0) : C(by[c + q]);
-        P.fyh[q] = wyh ? C(0) : C(by[c + q + P.yp]);
-        P.fzl[q] = wzl ? C(0) : C(bz[c + q]);
-        P.fzh[q] = wzh ? C(0) : C(bz[c + q + P.zp]);
-        P.r[q] = R[c + q];
-        P.sg[q] = sg ? C(sg[c + q]) : C(0);
-    }
-    P.dg[0] = (P.fx0 + P.fx1) + (P.fyl[0] + P.fyh[0]) + (P.fzl[0] + P.fzh[0]);
-    P.dg[1] = (P.fx1 + P.fx2) + (P.fyl[1] + P.fyh[1]) + (P.fzl[1] + P.fzh[1]);
-    if (sg) {                  // h^2 sigma, the general operator's diagonal term
-        P.dg[0] += P.sg[0];
-        P.dg[1] += P.sg[1];
-    }
-}
-
-// Over-relaxed Gauss-Seidel update of the cell of colour `colour` in the pair
-// (eq. beta_pressure, relaxation om); zero: e is zero on entry (neither the
-// cell nor its neighbours are read); self_zero: the cell's own old value is
-// zero (the second colour of the first sweep), its neighbours are read.
-template <typename C>
-__device__ __forceinline__ void tp_gs(const TPair<C> &P, C *E, C h2, C om, int colour, bool zero,
-                                      bool self_zero)
-{
-    if (!P.on)
-        return;
-    const int q = colour == P.par ? 0 : 1;
-    const int c = P.c + q;
-    const C xl = q == 0 ? P.fx0 : P.fx1, xh = q == 0 ? P.fx1 : P.fx2;
-    C s = C(0);
-    if (!zero)
-        s = xl * E[q == 0 ? P.xm : P.c] + xh * E[q == 0 ? P.c + 1 : P.xp] + P.fyl[q] * E[c + P.ym] +
-            P.fyh[q] * E[c + P.yp] + P.fzl[q] * E[c + P.zm] + P.fzh[q] * E[c + P.zp];
-    const C g = (s - h2 * P.r[q]) / P.dg[q];
-    const C v = (zero || self_zero) ? om * g : (C(1) - om) * E[c] + om * g;
-    // a cell with no open face and no diagonal term is excluded: it stays 0
-    E[c] = P.dg[q] > C(0) ? v : C(0);
-}
-
-// r - A e at the two cells of the pair, summed (the restriction adds four pairs)
-template <typename C>
-__device__ __forceinline__ C tp_residual_sum(const TPair<C> &P, const C *E, C ih2)
-{
-    C acc = C(0);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int c = P.c + q;
-        const C xl = q == 0 ? P.fx0 : P.fx1, xh = q == 0 ? P.fx1 : P.fx2;
-        const C ec = E[c];
-        const C exm = E[q == 0 ? P.xm : P.c], exp = E[q == 0 ? P.c + 1 : P.xp];
-        const C fl = xh * (exp - ec) - xl * (ec - exm) + P.fyh[q] * (E[c + P.yp] - ec) -
-                     P.fyl[q] * (ec - E[c + P.ym]) + P.fzh[q] * (E[c + P.zp] - ec) -
-                     P.fzl[q] * (ec - E[c + P.zm]);
-        acc += P.r[q] - ih2 * fl + ih2 * (P.sg[q] * ec);
-    }
-    return acc;
-}
-
-// e += P eH on the pair's two cells (the interpolation of k_prolong, with the
-// level's weights; w null: 1/4)
-template <typename C>
-__device__ __forceinline__ void tp_prolong(const TPair<C> &P, Dims fd, Bc bc, const C *EH, C *E,
-                                           const unsigned *w)
-{
-    if (!P.on)
-        return;
-    const Dims cd{fd.nx / 2, fd.ny / 2, fd.nz / 2};
-    const int nxy = fd.nx * fd.ny;
-    const int k = P.c / nxy, rem = P.c - k * nxy;
-    const int j = rem / fd.nx, i0 = rem - j * fd.nx;
-    const int I = i0 >> 1;
-    const int In[2] = {other_parent(i0, cd.nx, bc.x), other_parent(i0 + 1, cd.nx, bc.x)};
-    const int J0 = j >> 1, J1 = other_parent(j, cd.ny, bc.y);
-    const int K0 = k >> 1, K1 = other_parent(k, cd.nz, bc.z);
-    const int sy = cd.nx, sz = cd.nx * cd.ny;
-    const int rows[4] = {K0 * sz + J0 * sy, K0 * sz + J1 * sy, K1 * sz + J0 * sy, K1 * sz + J1 * sy};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const unsigned pw = w ? w[P.c + q] : 0x404040u;   // 64/256 = 1/4 on each axis
-        const C ax = C(pw & 255u) * C(1.0 / 256.0);
-        const C ay = C((pw >> 8) & 255u) * C(1.0 / 256.0);
-        const C az = C((pw >> 16) & 255u) * C(1.0 / 256.0);
-        C xv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const C cI = EH[rows[u] + I];
-            xv[u] = cI + ax * (EH[rows[u] + In[q]] - cI);
-        }
-        const C y0 = xv[0] + ay * (xv[1] - xv[0]);
-        const C y1 = xv[2] + ay * (xv[3] - xv[2]);
-        E[P.c + q] += y0 + az * (y1 - y0);
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(TAIL_THREADS) void k_tail_cycle(TailArgs<T> a)
-{
-    using C = typename Acc<T>::type;
-    constexpr bool BLDS = sizeof(C) == 4;   // FP32 arithmetic: face coefficients in LDS too
-    constexpr int SPW = (TAIL_LDS / 2 * (int)sizeof(C) + 7) / 8;
-    static_assert(SPW >= 1024, "the coarsest right-hand side reuses the pair sums' storage");
-    static_assert(TAIL_CELLS % TAIL_THREADS == 0 && TAIL_PINV % TAIL_THREADS == 0, "staging");
-    __shared__ C E[TAIL_LDS];
-    __shared__ C Rr[TAIL_LDS];
-    __shared__ C Bs[BLDS ? 3 : 1][BLDS ? TAIL_LDS : 1];
-    __shared__ unsigned Wl[TAIL_LDS];      // prolongation weights of every level but the last
-    __shared__ double Pv[TAIL_PINV];       // the coarsest pseudo-inverse, when it fits
-    // per-pair residual sums during the restrictions, then the coarsest
-    // right-hand side (the last restriction has finished reading the sums)
-    __shared__ double SpRaw[SPW];
-    C *Sp = reinterpret_cast<C *>(SpRaw);
-    double *rs = SpRaw;
-    const int L = a.n;
-    const int tid = threadIdx.x;
-    const C om = static_cast<C>(a.omega);
-    int off[TAIL_MAX + 1];                  // first cell of level q in the LDS arrays
-    off[0] = 0;
-    for (int l = 0; l < L; ++l)
-        off[l + 1] = off[l] + (int)cells(a.d[l]);
-    // Stage the input right-hand side, the coefficients, the weights and a
-    // small pseudo-inverse.  Every load is issued before the first LDS store,
-    // so the staging costs one memory round trip.  The first level has at
-    // most TAIL_CELLS cells (a fixed count per thread, indices clamped so that
-    // every load is in range); the levels below it together hold fewer than
-    // an eighth as many, at most one cell per thread.
-    constexpr int U0 = TAIL_CELLS / TAIL_THREADS;
-    constexpr int UP = TAIL_PINV / TAIL_THREADS;
-    const int n0 = off[1];
-    const int nrest = off[L] - n0;
-    const int nwt = off[L - 1];             // weights: every level but the last
-    const int nc = a.ncoarse;
-    const bool pvl = nc * nc <= TAIL_PINV;
-    const unsigned WDEF = 0x404040u;        // 64/256 = 1/4 on each axis: trilinear
-    C r0[U0], b0[3][U0], b1[3] = {C(0), C(0), C(0)}, e0[U0];
-    unsigned w0[U0], w1 = WDEF;
-    double pv[UP];
-    const unsigned *wf = L > 1 ? a.w[0] : nullptr;
-#pragma unroll
-    for (int u = 0; u < U0; ++u) {
-        const int cc = min(tid + u * TAIL_THREADS, n0 - 1);
-        r0[u] = ld(a.r[0], cc);
-        e0[u] = a.warm ? ld(a.e[0], cc) : C(0);
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-            b0[m][u] = BLDS ? ld(a.b[0][m], cc) : C(0);
-        w0[u] = wf ? wf[cc] : WDEF;
-    }
-    // this thread's cell of the levels below the first: its level's arrays
-    // are picked by selects over the (uniform) argument pointers, so that no
-    // load waits for another
-    const int g = n0 + tid;
-    const T *pb[3] = {nullptr, nullptr, nullptr};
-    const unsigned *pw = nullptr;
-    int ob = 0;
-#pragma unroll
-    for (int q = 1; q < TAIL_MAX; ++q)
-        if (q < L && g >= off[q]) {
-#pragma unroll
-            for (int m = 0; m < 3; ++m)
-                pb[m] = a.b[q][m];
-            pw = a.w[q];
-            ob = off[q];
-        }
-    const bool rin = tid < nrest;
-    const bool win = rin && g < nwt;
-    if (rin) {
-        if (BLDS)
-#pragma unroll
-            for (int m = 0; m < 3; ++m)
-                b1[m] = ld(pb[m], g - ob);
-        if (win && pw)
-            w1 = pw[g - ob];
-    }
-#pragma unroll
-    for (int u = 0; u < UP; ++u) {
-        const int i = tid + u * TAIL_THREADS;
-        pv[u] = pvl ? a.pinv[min(i, nc * nc - 1)] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U0; ++u) {
-        const int cc = tid + u * TAIL_THREADS;
-        if (cc < n0) {
-            Rr[cc] = r0[u];
-            if (a.warm)
-                E[cc] = e0[u];
-            if (BLDS)
-#pragma unroll
-                for (int m = 0; m < 3; ++m)
-                    Bs[BLDS ? m : 0][BLDS ? cc : 0] = b0[m][u];
-            if (L > 1)
-                Wl[cc] = w0[u];
-        }
-    }
-    if (rin) {
-        if (BLDS)
-#pragma unroll
-            for (int m = 0; m < 3; ++m)
-                Bs[BLDS ? m : 0][BLDS ? g : 0] = b1[m];
-        if (win)
-            Wl[g] = w1;
-    }
-    if (pvl)
-#pragma unroll
-        for (int u = 0; u < UP; ++u)
-            if (tid + u * TAIL_THREADS < nc * nc)
-                Pv[tid + u * TAIL_THREADS] = pv[u];
-    __syncthreads();
-    TPair<C> P[TAIL_PAIRS];
-    auto visit = [&](int l) {
-#pragma unroll
-        for (int u = 0; u < TAIL_PAIRS; ++u) {
-            const C h2 = (C)a.h2[l];
-            if (BLDS)
-                tp_load(P[u], a.d[l], a.bc, tid + u * TAIL_THREADS, &Bs[0][BLDS ? off[l] : 0],
-                        &Bs[BLDS ? 1 : 0][BLDS ? off[l] : 0], &Bs[BLDS ? 2 : 0][BLDS ? off[l] : 0],
-                        Rr + off[l], a.s[l], h2);
-            else
-                tp_load(P[u], a.d[l], a.bc, tid + u * TAIL_THREADS, a.b[l][0], a.b[l][1], a.b[l][2],
-                        Rr + off[l], a.s[l], h2);
-        }
-    };
-    for (int l = 0; l + 1 < L; ++l) {
-        const C h2 = (C)a.h2[l];
-        C *El = E + off[l];
-        visit(l);
-        for (int sw = 0; sw < a.nu_pre; ++sw)
-            for (int colour = 0; colour < 2; ++colour) {
-#pragma unroll
-                for (int u = 0; u < TAIL_PAIRS; ++u)
-                    tp_gs(P[u], El, h2, om, colour, sw == 0 && colour == 0 && !(a.warm && l == 0),
-                          sw == 0 && !(a.warm && l == 0));
-                __syncthreads();
-            }
-        // restriction: residual sums per pair, then four pairs per coarse cell
-        const int np = (int)cells(a.d[l]) / 2;
-#pragma unroll
-        for (int u = 0; u < TAIL_PAIRS; ++u)
-            if (P[u].on)
-                Sp[tid + u * TAIL_THREADS] = tp_residual_sum(P[u], El, C(1) / h2);
-        __syncthreads();
-        const Dims fd = a.d[l];
-        const int hx = fd.nx / 2;
-        const Dims cd{fd.nx / 2, fd.ny / 2, fd.nz / 2};
-        for (int cc = tid; cc < (int)cells(cd); cc += TAIL_THREADS) {
-            const int K = cc / (cd.nx * cd.ny), rem = cc - K * cd.nx * cd.ny;
-            const int J = rem / cd.nx, I = rem - J * cd.nx;
-            const int p00 = ((2 * K) * fd.ny + 2 * J) * hx + I;
-            const int sy = hx, sz = hx * fd.ny;
-            Rr[off[l + 1] + cc] = C(0.125) * ((Sp[p00] + Sp[p00 + sy]) + (Sp[p00 + sz] + Sp[p00 + sz + sy]));
-        }
-        (void)np;
-        __syncthreads();
-    }
-    // coarsest level: e = A^+ r in FP64, g threads per output reduced by shuffles
-    {
-        const int n = a.ncoarse;
-        for (int t = tid; t < n; t += TAIL_THREADS)
-            rs[t] = static_cast<double>(Rr[off[L - 1] + t]);
-        __syncthreads();
-        int gs = 1;
-        while (gs < 64 && 2 * gs * n <= TAIL_THREADS)
-            gs *= 2;
-        const int outp = tid / gs, lane = tid % gs;
-        double s = 0.0;
-        if (outp < n) {
-            if (pvl)
-                for (int jj = lane; jj < n; jj += gs)
-                    s += Pv[jj * n + outp] * rs[jj];
-            else
-                for (int jj = lane; jj < n; jj += gs)
-                    s += a.pinv[(size_t)jj * n + outp] * rs[jj];
-        }
-        for (int o = gs >> 1; o > 0; o >>= 1)
-            s += __shfl_xor(s, o, 64);
-        if (lane == 0 && outp < n)
-            E[off[L - 1] + outp] = static_cast<C>(s);
-        __syncthreads();
-    }
-    for (int l = L - 2; l >= 0; --l) {
-        const C h2 = (C)a.h2[l];
-        C *El = E + off[l];
-        visit(l);
-#pragma unroll
-        for (int u = 0; u < TAIL_PAIRS; ++u)
-            tp_prolong(P[u], a.d[l], a.bc, E + off[l + 1], El, Wl + off[l]);
-        __syncthreads();
-        for (int sw = 0; sw < a.nu_post; ++sw)
-            for (int colour = 1; colour >= 0; --colour) {
-#pragma unroll
-                for (int u = 0; u < TAIL_PAIRS; ++u)
-                    tp_gs(P[u], El, h2, om, colour, false, false);
-                __syncthreads();
-            }
-    }
-    // the correction of the tail's first level goes back to global memory
-    for (int c = tid; c < off[1]; c += TAIL_THREADS)
-        a.e[0][c] = static_cast<T>(E[c]);
 }
 
 template <typename T>
@@ -2573,34 +2183,6 @@ void launch_prolong_weights(Dims d, Bc bc, const double *bx, const double *by, c
 }
 
 template <typename T>
-void launch_tail(int nlev, const Dims *d, const double *h2, const void *const (*b)[3], void *const *e,
-                 void *const *r, const void *const *sg, const unsigned *const *w, Bc bc,
-                 int nu_pre, int nu_post, double omega, const double *pinv, int ncoarse,
-                 bool warm, hipStream_t s)
-{
-    TailArgs<T> a;
-    a.n = nlev;
-    for (int l = 0; l < nlev; ++l) {
-        a.d[l] = d[l];
-        a.h2[l] = h2[l];
-        for (int m = 0; m < 3; ++m)
-            a.b[l][m] = (const T *)b[l][m];
-        a.w[l] = w ? w[l] : nullptr;
-        a.e[l] = (T *)e[l];
-        a.r[l] = (T *)r[l];
-        a.s[l] = (const T *)sg[l];
-    }
-    a.bc = bc;
-    a.nu_pre = nu_pre;
-    a.nu_post = nu_post;
-    a.omega = omega;
-    a.warm = warm ? 1 : 0;
-    a.pinv = pinv;
-    a.ncoarse = ncoarse;
-    hipLaunchKernelGGL((k_tail_cycle<T>), dim3(1), dim3(TAIL_THREADS), 0, s, a);
-}
-
-template <typename T>
 int launch_convert_scaled(size_t n, const double *src, double scale, double limit, T *dst,
                           double *part, int max_blocks, hipStream_t s)
 {
@@ -2930,10 +2512,6 @@ void launch_sub_mean(size_t n, double *x, const double *scal, int slot, const un
     template int launch_load_density<T>(Dims, Bc, const double *, double *const[3], T *const[3], \
                                         double *const[3], double *, unsigned *, double *,       \
                                         hipStream_t);                                           \
-    template void launch_tail<T>(int, const Dims *, const double *, const void *const (*)[3],   \
-                                 void *const *, void *const *, const void *const *,             \
-                                 const unsigned *const *, Bc, int, int, double, const double *, \
-                                 int, bool, hipStream_t);                                       \
     template void launch_convert<T>(size_t, const double *, T *, hipStream_t);                  \
     template int launch_convert_scaled<T>(size_t, const double *, double, double, T *, double *, \
                                           int, hipStream_t);                                    \
