@@ -755,7 +755,7 @@ void *fused_sweeps(pp_ctx *c, LevelBuf &v, int l, int nu, void *cur, int first_c
                 const int np = launch_rbgs_fused2<T>(
                     v.d, c->bc, b0, b1, b2, (const T *)v.r, (const T *)cur, (T *)out,
                     (const T *)v.s, h2, c->opts.omega, first_colour, zero, s,
-                    (last && dot) ? c->part : nullptr);
+                    (last && dot) ? c->part : nullptr, 3 * (long long)c->pstride);
                 if (last && np > 0)
                     c->dot_np = np;
                 two = true;
@@ -1665,7 +1665,7 @@ int check_smooth2_dot(const char *who, const pp_grid *grid, const float *bx, con
     const Dims d = to_dims(grid);
     if (!fused2_fits(d))
         return fail(PP_EINVAL, w + ": every cell count must be >= 8");
-    // at most one partial per workgroup: tiles x z chunks of >= 8 planes
+    // the workgroup partials the launch may write: tiles x z chunks of 8 planes
     *nparts_max = (size_t)((d.nx + 63) / 64) * ((d.ny + 7) / 8) * ((d.nz + 7) / 8);
     return PP_OK;
 }
@@ -2068,7 +2068,7 @@ int pp_k_smooth2_fused_dot_f32(const pp_grid *grid, const float *bx, const float
     hipStream_t s = (hipStream_t)hip_stream;
     const int np = launch_rbgs_fused2<float>(d, to_bc(grid), bx, by, bz, r, e_in, e_out, nullptr,
                                              grid->h * grid->h, omega, first_colour, false, s,
-                                             part);
+                                             part, (long long)nparts_max);
     int rc = PP_OK;
     if (np <= 0 || (size_t)np > nparts_max)
         rc = fail(PP_EHIP, "pp_k_smooth2_fused_dot_f32: unexpected workgroup count");
@@ -2097,11 +2097,11 @@ int pp_k_smooth2_fused_dot_f32_noalloc(const pp_grid *grid, const float *bx, con
     hipStream_t s = (hipStream_t)hip_stream;
     double *part = nullptr;
     PP_TRY(noalloc_scratch(s, &part));
-    // the launch takes z chunks of at least 8 planes, so it never uses more
-    // than nparts_max partial sums (checked above against the array size)
+    // the launch writes at most nparts_max partial sums (checked above against
+    // the array size)
     const int np = launch_rbgs_fused2<float>(to_dims(grid), to_bc(grid), bx, by, bz, r, e_in,
                                              e_out, nullptr, grid->h * grid->h, omega,
-                                             first_colour, false, s, part);
+                                             first_colour, false, s, part, (long long)nparts_max);
     PP_TRY(check_launch("pp_k_smooth2_fused_dot_f32_noalloc"));
     if (np <= 0 || (size_t)np > nparts_max)
         return fail(PP_EHIP, "pp_k_smooth2_fused_dot_f32_noalloc: unexpected workgroup count");

@@ -430,17 +430,39 @@ static long long fused_slots()
 // less there than the register copies at the back edge of the other form.
 constexpr int WHOLE_MIN_STEPS = 48;
 
-// Chunk length along z: the smallest chunk (fewest redundant halo planes)
-// whose workgroups all fit on the GPU at once, so a sweep runs as a single
-// round of resident workgroups with no tail.
-static int fused_kz(Dims d, unsigned tiles, long long slots)
+// Chunk length along z.  A chunk of kz planes marches kz + halo plane steps
+// (halo: the planes beyond its ends, recomputed) and takes the time of about
+// two more to start; `slots` workgroups are resident at once, so the pass takes
+// rounds x (kz + halo + 2) steps, and the chunk that makes this least is used
+// (the longest of equals: less recomputed).  It is at least kmin planes, in at
+// most max_chunks chunks.  Where the tiles do not divide the slots,
+// the chunk that fills them exactly leaves a few workgroups to a second round:
+// 96 x 80 x 112 (20 tiles): 13 chunks of 9 planes, 260 workgroups on 256 CUs,
+// 22.4 us zero start; 12 chunks of 10 planes, one round, 15.1 us.
+static int chunk_planes(int nz, long long tiles, long long slots, int halo, int kmin,
+                        long long max_chunks)
 {
-    long long kz = ((long long)d.nz * tiles + slots - 1) / slots;
-    if (kz < 4)
-        kz = 4;
-    if (kz > d.nz)
-        kz = d.nz;
-    return (int)kz;
+    int best = nz;
+    long long cost = -1;
+    if (kmin > nz)
+        kmin = nz;
+    // the most chunks that R rounds hold, R = 1, 2, ...
+    for (long long R = (tiles + slots - 1) / slots, R1 = R + 16; R < R1; ++R) {
+        long long m = R * slots / tiles;
+        if (m > max_chunks)
+            m = max_chunks;
+        int kz = (int)((nz + m - 1) / m);
+        if (kz < kmin)
+            kz = kmin;
+        const long long c = (tiles * ((nz + kz - 1) / kz) + slots - 1) / slots * (kz + halo + 2);
+        if (cost < 0 || c < cost) {
+            cost = c;
+            best = kz;
+        }
+        if (kz == kmin || m == max_chunks)
+            break;
+    }
+    return best;
 }
 
 template <typename T>
@@ -461,7 +483,7 @@ void launch_rbgs_fused(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
     const unsigned tx = (d.nx + FTX - 1) / FTX, ty = (d.ny + FTY - 1) / FTY;
     const long long slots = sg ? (zero ? fused_slots<T, true, true>() : fused_slots<T, false, true>())
                                : (zero ? fused_slots<T, true, false>() : fused_slots<T, false, false>());
-    const int kz = fused_kz(d, tx * ty, slots);
+    const int kz = chunk_planes(d.nz, (long long)tx * ty, slots, 2, 4, d.nz);
     const unsigned tz = (d.nz + kz - 1) / kz;
     const dim3 grid(tx * ty, tz);   // distinct shapes per level in profiles
     const bool whole = kz + 2 >= WHOLE_MIN_STEPS;   // a chunk marches kz + 2 steps
@@ -894,7 +916,7 @@ void prepare_fused2()
 template <typename T>
 int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, const T *r,
                        const T *ein, T *eout, const T *sg, double h2, double omega,
-                       int first_colour, bool zero, hipStream_t s, double *part)
+                       int first_colour, bool zero, hipStream_t s, double *part, long long max_parts)
 {
     const unsigned tx = (d.nx + GTX - 1) / GTX, ty = (d.ny + GTY - 1) / GTY;
     // the fused dot product: FP32 regular passes without a diagonal term
@@ -907,20 +929,10 @@ int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
                            : fused2_slots<T, false, true, false>())
                    : (zero ? fused2_slots<T, true, false, false>()
                            : fused2_slots<T, false, false, false>());
-    // Chunk length: the shortest that keeps every workgroup resident at once
-    // (a single round), but at least two planes.  A chunk marches six planes
-    // beyond its own, recomputed; on small levels, whose workgroups leave most
-    // CUs idle, short chunks cost no time and shorten the march, which sets
-    // the pass's duration there.  The pass that forms the dot product keeps
-    // chunks of at least 8 planes, so that its workgroup partials stay within
-    // the reduction buffer (sized for the grid of the reduction kernels).
-    long long kzl = ((long long)d.nz * tx * ty + slots - 1) / slots;
-    const int kmin = dot ? 8 : 2;
-    if (kzl < kmin)
-        kzl = kmin;
-    if (kzl > d.nz)
-        kzl = d.nz;
-    const int kz = (int)kzl;
+    // chunks of at least two planes; a pass that forms the dot product writes a
+    // partial sum per workgroup, at most max_parts of them
+    const long long tiles = (long long)tx * ty;
+    const int kz = chunk_planes(d.nz, tiles, slots, 6, 2, dot ? max_parts / tiles : d.nz);
     const unsigned tz = (d.nz + kz - 1) / kz;
     const dim3 grid(tx * ty, tz);
     // a chunk marches kz + 6 steps; FP16 keeps the exit after every step
@@ -960,11 +972,11 @@ template void prepare_fused2<float>();
 template void prepare_fused2<_Float16>();
 template int launch_rbgs_fused2<float>(Dims, Bc, const float *, const float *, const float *,
                                        const float *, const float *, float *, const float *, double,
-                                       double, int, bool, hipStream_t, double *);
+                                       double, int, bool, hipStream_t, double *, long long);
 template int launch_rbgs_fused2<_Float16>(Dims, Bc, const _Float16 *, const _Float16 *,
                                           const _Float16 *, const _Float16 *, const _Float16 *,
                                           _Float16 *, const _Float16 *, double, double, int, bool,
-                                          hipStream_t, double *);
+                                          hipStream_t, double *, long long);
 
 #define PP_INSTANTIATE_FUSED(T)                                                                  \
     template void prepare_fused<T>();                                                           \
