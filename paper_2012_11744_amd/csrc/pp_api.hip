@@ -1519,6 +1519,7 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
     c->opts = o;
     c->stream = (hipStream_t)hip_stream;
     c->d = to_dims(grid);
+    c->d.fixed_order = o.precision == PP_MIXED_FP16;
     c->bc = to_bc(grid);
     c->N = cells(c->d);
     c->nlev = nlev;
@@ -1570,7 +1571,7 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
         rc = dev_alloc_t(c, &c->d64b, sizeof(double) * c->N);
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->q64, sizeof(double) * c->N);
-    c->pstride = grid_blocks(red_grid(c->d));
+    c->pstride = partials_max(c->d);
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->part, sizeof(double) * 6 * c->pstride);   // rows 3..5: pp_step's side stream
     if (rc == PP_OK)

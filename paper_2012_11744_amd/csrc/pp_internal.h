@@ -39,6 +39,12 @@ constexpr int BLOCK = BX * BY;
 
 struct Dims {
     int nx, ny, nz;
+    // Reductions over this grid keep blocks of 8 planes and with them the order
+    // of their sums (level 0 of an FP16-storage context).  There a change in the
+    // last bit of a scalar, by way of one rounding of the stored direction,
+    // reaches the FP16 roundings of the V-cycle and through them every cell: the
+    // iterates repeat only with the sums.
+    int fixed_order = 0;
 };
 
 // 1 = wall in that direction, 0 = periodic.
@@ -82,12 +88,72 @@ inline dim3 colour_grid(Dims d)
 
 inline size_t grid_blocks(dim3 g) { return (size_t)g.x * g.y * g.z; }
 
-// kernels that also reduce walk RZ planes per block: fewer partial sums
-constexpr int RZ = 8;
+// Kernels that reduce, and the density load, walk several planes per block
+// (fewer partial sums, neighbours from cache), but no more than leave 2048
+// blocks, eight per CU: on a small grid a walk is a chain of memory round
+// trips on a few CUs (32^3 in blocks of 8 planes: 16 blocks, 33 us for the
+// density load, 12 us in blocks of one coarse plane).  A kernel takes its
+// planes per block from its grid (block_planes).
+inline int walk_planes(int nz, size_t xy_blocks, int most)
+{
+    while (most > 1 && xy_blocks * ((nz + most - 1) / most) < 2048)
+        most /= 2;
+    return most;
+}
+
 inline dim3 red_grid(Dims d)
 {
-    return dim3((d.nx + BX - 1) / BX, (d.ny + BY - 1) / BY, (d.nz + RZ - 1) / RZ);
+    const unsigned gx = (d.nx + BX - 1) / BX, gy = (d.ny + BY - 1) / BY;
+    const int rz = d.fixed_order ? 8 : walk_planes(d.nz, (size_t)gx * gy, 8);
+    return dim3(gx, gy, (d.nz + rz - 1) / rz);
 }
+
+// Grid of a kernel with 2 x 2 cells per thread that carries a column's planes
+// (the direction pass and the residual): its walk also reads a plane beyond
+// each end.  The longest chunk of up to 8 planes that leaves two blocks per
+// CU; with an FP64 direction (wide: half the registers' worth of blocks fits a
+// CU, twice the bytes are read again at a chunk's ends) chunks of 8 already
+// where they leave one.  Direction pass in chunks of 8 planes / as taken: 32^3
+// FP64 18.6 / 5.7 us (1 plane), 64^3 14.0 / 6.8 us (1), 96 x 80 x 112
+// 18.5 / 14.3 us (2), 128^3 20.3 / 19.8 us (4); 128^3 FP64 25.0 us in 8, 28.8 in
+// 4; at 256^3 the length does not matter (1 to 16 planes).
+inline dim3 quad_grid(Dims d, bool wide)
+{
+    const unsigned gx = (d.nx / 2 + BX - 1) / BX, gy = (d.ny / 2 + BY - 1) / BY;
+    const size_t xy = (size_t)gx * gy;
+    int kz = 8;
+    if (!d.fixed_order && !(wide && xy * ((d.nz + 7) / 8) >= 256))
+        while (kz > 1 && xy * ((d.nz + kz - 1) / kz) < 512)
+            kz /= 2;
+    return dim3(gx, gy, (d.nz + kz - 1) / kz);
+}
+
+// grid of the one-pass coefficient loads: a thread per coarse column
+inline dim3 load_grid(Dims fd)
+{
+    const unsigned gx = (fd.nx / 2 + BX - 1) / BX, gy = (fd.ny / 2 + BY - 1) / BY;
+    const int kz = walk_planes(fd.nz / 2, (size_t)gx * gy, 4);
+    return dim3(gx, gy, (fd.nz / 2 + kz - 1) / kz);
+}
+
+// partial sums a reducing launch may write per quantity
+inline size_t partials_max(Dims d)
+{
+    size_t n = grid_blocks(red_grid(d));
+    if (n < grid_blocks(load_grid(d)))
+        n = grid_blocks(load_grid(d));
+    if (n < grid_blocks(quad_grid(d, false)))
+        n = grid_blocks(quad_grid(d, false));
+    return n < 4096 ? 4096 : n;
+}
+
+#if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
+// planes per block of a grid whose z extent is ceil(nz / planes)
+__device__ __forceinline__ int block_planes(int nz)
+{
+    return (int)((nz + gridDim.z - 1) / gridDim.z);
+}
+#endif
 
 // ---------------------------------------------------------------------------
 // scalar slots of the device scalar array used by the outer iterations

@@ -829,8 +829,9 @@ __global__ __launch_bounds__(BLOCK) void k_load_density(Dims fd, Bc bc, const do
         const int xu = (x + 2 == fd.nx) ? 0 : x + 2;
         const int yu = (y + 2 == fd.ny) ? 0 : y + 2, yu3 = (yu + 1 == fd.ny) ? 0 : yu + 1;
         const bool wxu = bc.x && xu == 0, wyu = bc.y && yu == 0;
-        const int Ke = min(cd.nz, ((int)blockIdx.z + 1) * (RZ / 2));
-        for (int K = blockIdx.z * (RZ / 2); K < Ke; ++K) {
+        const int kz = block_planes(cd.nz);
+        const int Ke = min(cd.nz, ((int)blockIdx.z + 1) * kz);
+        for (int K = blockIdx.z * kz; K < Ke; ++K) {
             const int z = 2 * K;
             const int zm2 = (z < 2) ? z - 2 + fd.nz : z - 2;
             const int zu = (z + 2 == fd.nz) ? 0 : z + 2, zu3 = (zu + 1 == fd.nz) ? 0 : zu + 1;
@@ -946,8 +947,9 @@ __global__ __launch_bounds__(BLOCK) void k_check_rho(Dims d, const double *__res
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const double r = rho[((size_t)k * d.ny + j) * d.nx + i];
             if (!(r > 0.0 && r < INFINITY))
                 v[0] += 1.0;
@@ -967,8 +969,9 @@ __global__ __launch_bounds__(BLOCK) void k_check_beta(Dims d, Bc bc, const doubl
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
             const double b[3] = {bx[c], by[c], bz[c]};
             const bool wall[3] = {bc.x && i == 0, bc.y && j == 0, bc.z && k == 0};
@@ -990,8 +993,9 @@ __global__ __launch_bounds__(BLOCK) void k_check_sigma(Dims d, const double *__r
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[2] = {0.0, 0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const double x = sg[((size_t)k * d.ny + j) * d.nx + i];
             if (!(x >= 0.0 && x < INFINITY))
                 v[0] += 1.0;
@@ -1015,8 +1019,9 @@ __global__ __launch_bounds__(BLOCK) void k_active(Dims d, Bc bc, const double *_
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
             const Links<double> L = links(n, bx, by, bz);
             const double dg = (L.xl + L.xh) + (L.yl + L.yh) + (L.zl + L.zh) + (sg ? sg[n.c] : 0.0);
@@ -1105,7 +1110,7 @@ __global__ __launch_bounds__(BLOCK) void k_divergence(Dims d, Bc bc, const doubl
     out[n.c] = s_h * ((xh - xl) + (yh - yl) + (zh - zl));
 }
 
-// k_divergence for the pressure operator (no face coefficients) walking RZ
+// k_divergence for the pressure operator (no face coefficients) walking several
 // planes per thread, which also sums the values it writes, in the blocks and
 // the order of k_sum: the partials are those k_sum would form from `out`,
 // bit for bit, so the right-hand side's mean needs no pass of its own
@@ -1124,8 +1129,9 @@ __global__ __launch_bounds__(BLOCK) void k_divergence_sum(Dims d, Bc bc,
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
             const double xl = n.wxl ? 0.0 : ux[n.c], xh = n.wxh ? 0.0 : ux[n.xp];
             const double yl = n.wyl ? 0.0 : uy[n.c], yh = n.wyh ? 0.0 : uy[n.yp];
@@ -1266,8 +1272,9 @@ __global__ __launch_bounds__(BLOCK) void k_sum(Dims d, const double *__restrict_
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
             if (!act || act[c])
                 v[0] += x[c];
@@ -1434,8 +1441,9 @@ __global__ __launch_bounds__(BLOCK) void k_residual(Dims d, Bc bc, const double 
     double v[3] = {0.0, 0.0, 0.0};
     if (i < d.nx && j < d.ny) {
         const double mean = scal[S_MEAN];
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
             // the right-hand side of an excluded cell is not part of the system
             const bool on = !act || act[n.c];
@@ -1461,7 +1469,7 @@ __global__ __launch_bounds__(BLOCK) void k_residual(Dims d, Bc bc, const double 
 }
 
 // k_residual (x given, the same three partial sums) for grids with even nx and ny and 16-byte aligned
-// arrays: each thread owns a 2 x 2 block of cells and walks RZ planes with the
+// arrays: each thread owns a 2 x 2 block of cells and walks a chunk of planes with the
 // column's planes below and at the current one carried in registers, as in
 // k_dir_apply2; the same per-cell arithmetic as the one-cell kernel.  RHO: the
 // link coefficients are formed from the cell densities by the expression the
@@ -1510,8 +1518,9 @@ __global__ __launch_bounds__(BLOCK) void k_residual2(Dims d, Bc bc, const double
             o[3] = c.y;
         };
         // cells 0: (x0, j0), 1: (x0 + 1, j0), 2: (x0, j1), 3: (x0 + 1, j1)
-        const int k0 = (int)gbz * RZ;
-        const int ke = min(d.nz, k0 + RZ);
+        const int kz = block_planes(d.nz);
+        const int k0 = (int)gbz * kz;
+        const int ke = min(d.nz, k0 + kz);
         const size_t pm0 = (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz;
         double Xm[4], Xc[4], ZL[4], Rc[4];
         quad(x, pm0, Xm);
@@ -1641,8 +1650,9 @@ __global__ __launch_bounds__(BLOCK) void k_residual_T(Dims d, Bc bc, const doubl
     if (i < d.nx && j < d.ny) {
         const double mean = scal[S_MEAN];
         const double inv = 1.0 / scal[S_NEXT];
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
             const Links<double> L = links(n, bx, by, bz);
             double ax = ih2 * flux_sum(n, L, x);
@@ -1688,8 +1698,9 @@ __global__ __launch_bounds__(BLOCK) void k_dot_rz(Dims d, const double *__restri
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
             v[0] += r[c] * static_cast<double>(z[c]);
         }
@@ -1709,7 +1720,7 @@ __global__ __launch_bounds__(BLOCK) void k_dot_rz(Dims d, const double *__restri
 // fma (so the same bits), which is why D_new and D_old are different buffers.
 // The second partial is D_old . q, from which the flexible coefficient's
 // r_{k+1} . z_k follows without a pass over z_k (see OP_ALPHA).
-// Each thread walks a column of RZ planes and carries the column's values of
+// Each thread walks a column of planes and carries the column's values of
 // the planes below and above (D_new, and the low z-face coefficient) in
 // registers.  The iterate's updates are applied here, where D_old is read
 // anyway, two directions at a time: MODE == DIR_TWO adds a_{k-2} D_{k-2}
@@ -1758,8 +1769,9 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply(Dims d, Bc bc, const double
         const ptrdiff_t oyp = (j == d.ny - 1) ? -(ptrdiff_t)(d.ny - 1) * d.nx : (ptrdiff_t)d.nx;
         const bool wxl = bc.x && i == 0, wxh = bc.x && i == d.nx - 1;
         const bool wyl = bc.y && j == 0, wyh = bc.y && j == d.ny - 1;
-        const int k0 = blockIdx.z * RZ;
-        const int ke = min(d.nz, k0 + RZ);
+        const int kz = block_planes(d.nz);
+        const int k0 = blockIdx.z * kz;
+        const int ke = min(d.nz, k0 + kz);
         const size_t cm0 = col + (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz;
         double dm = dv(cm0), dc = dv(col + (size_t)k0 * sz);
         double rc = 0.0, zl;
@@ -1887,8 +1899,9 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
             return *reinterpret_cast<const F2 *>(p + c);
         };
         // cells 0: (x0, j0), 1: (x0 + 1, j0), 2: (x0, j1), 3: (x0 + 1, j1)
-        const int k0 = (int)gbz * RZ;
-        const int ke = min(d.nz, k0 + RZ);
+        const int kz = block_planes(d.nz);
+        const int k0 = (int)gbz * kz;
+        const int ke = min(d.nz, k0 + kz);
         const size_t pm = (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz, pc0 = (size_t)k0 * sz;
         double Dm[4], Dc[4], Oc[4], ZL[4], Rc[4], t0, t1;
         dv2(pm + o0, Dm[0], Dm[1], t0, t1);
@@ -2052,8 +2065,9 @@ __global__ __launch_bounds__(BLOCK) void k_pcg_update(Dims d, const double *__re
     if (i < d.nx && j < d.ny) {
         const double alpha = scal[S_ALPHA];
         const double inv = 1.0 / scal[S_NEXT];
-        const int ke = min(d.nz, ((int)blockIdx.z + 1) * RZ);
-        for (int k = blockIdx.z * RZ; k < ke; ++k) {
+        const int kz = block_planes(d.nz);
+        const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
+        for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
             const double rn = r[c] - alpha * q[c];
             r[c] = rn;
@@ -2223,8 +2237,8 @@ int launch_load_coeffs(Dims fd, Bc bc, const double *const src[3], double *const
                        hipStream_t s, T *const coarseT[3])
 {
     const Dims cd{fd.nx / 2, fd.ny / 2, fd.nz / 2};
-    const int kz = part ? RZ / 2 : 1;
-    const dim3 g((cd.nx + BX - 1) / BX, (cd.ny + BY - 1) / BY, (cd.nz + kz - 1) / kz);
+    const dim3 g = part ? load_grid(fd) : cell_grid(cd);
+    const int kz = (cd.nz + (int)g.z - 1) / (int)g.z;
     T *ct[3] = {nullptr, nullptr, nullptr};
     if (coarseT)
         for (int m = 0; m < 3; ++m)
@@ -2245,8 +2259,7 @@ int launch_load_density(Dims fd, Bc bc, const double *rho, double *const dst[3],
                         double *const coarse[3], double *rcopy, unsigned *w0, double *part,
                         hipStream_t s)
 {
-    const Dims cd{fd.nx / 2, fd.ny / 2, fd.nz / 2};
-    const dim3 g((cd.nx + BX - 1) / BX, (cd.ny + BY - 1) / BY, (cd.nz + RZ / 2 - 1) / (RZ / 2));
+    const dim3 g = load_grid(fd);
     if (dstT[0])
         hipLaunchKernelGGL((k_load_density<T, true>), g, kBlock, 0, s, fd, bc, rho, dst[0], dst[1],
                            dst[2], dstT[0], dstT[1], dstT[2], coarse[0], coarse[1], coarse[2],
@@ -2382,13 +2395,14 @@ int launch_residual(Dims d, Bc bc, const double *bx, const double *by, const dou
     const bool quad = !zero_x && d.nx % 2 == 0 && d.ny % 2 == 0 &&
                       (((uintptr_t)x | (uintptr_t)b | (uintptr_t)r64) & 15) == 0;
     if (quad) {
-        const dim3 g((d.nx / 2 + BX - 1) / BX, (d.ny / 2 + BY - 1) / BY, (d.nz + RZ - 1) / RZ);
-        if (residual_from_rho(d, rho, b, x, r64))
+        const dim3 g = quad_grid(d, false);
+        if (residual_from_rho(d, rho, b, x, r64)) {
             hipLaunchKernelGGL(k_residual2<true>, g, kBlock, 0, s, d, bc, bx, by, bz, rho, b, scal,
                                x, sg, act, r64, ih2, part, pstride);
-        else
+        } else {
             hipLaunchKernelGGL(k_residual2<false>, g, kBlock, 0, s, d, bc, bx, by, bz, nullptr, b,
                                scal, x, sg, act, r64, ih2, part, pstride);
+        }
         return (int)grid_blocks(g);
     }
     if (zero_x)
@@ -2438,9 +2452,7 @@ int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const do
     using D = typename DirT<T>::type;
     // 2 x 2 cells per thread where the grid and the iterate allow pairs
     const bool quad = d.nx % 2 == 0 && d.ny % 2 == 0 && ((uintptr_t)x & 15) == 0;
-    const dim3 g = quad ? dim3((d.nx / 2 + BX - 1) / BX, (d.ny / 2 + BY - 1) / BY,
-                               (d.nz + RZ - 1) / RZ)
-                        : red_grid(d);
+    const dim3 g = quad ? quad_grid(d, sizeof(D) == 8) : red_grid(d);
     auto go = [&](auto kern) {
         PP_LAUNCH(kern, g, kBlock, 0, s, d, bc, bx, by, bz, rho, z, dold, dnew, q, x, sg,
                   scal, ih2, part, pstride);
