@@ -735,8 +735,8 @@ int load_coeffs(pp_ctx *c, const double *bx, const double *by, const double *bz)
 
 // nu out-of-place sweeps on a large level starting from the correction in
 // cur (ignored when zero_first), ping-ponging between e and e2; returns the
-// buffer holding the result.  FP32 and FP16 storage take two sweeps per pass
-// where the level allows it (the second pass of an odd nu is a single sweep).
+// buffer holding the result.  Two sweeps per pass where the level allows it (the
+// last pass of an odd nu is a single sweep).
 template <typename T>
 void *fused_sweeps(pp_ctx *c, LevelBuf &v, int l, int nu, void *cur, int first_colour,
                    bool zero_first, hipStream_t s, bool dot = false)
@@ -747,19 +747,16 @@ void *fused_sweeps(pp_ctx *c, LevelBuf &v, int l, int nu, void *cur, int first_c
         void *out = (cur == v.e) ? v.e2 : v.e;
         KT t(c, PP_KT_SMOOTH, l == 0);
         const bool zero = zero_first && sw == 0;
-        bool two = false;
-        if constexpr (!std::is_same<T, double>::value) {
-            if (sw + 2 <= nu && fused2_fits(v.d)) {
-                // the last pass may also form the outer loop's dot product
-                const bool last = sw + 2 == nu;
-                const int np = launch_rbgs_fused2<T>(
-                    v.d, c->bc, b0, b1, b2, (const T *)v.r, (const T *)cur, (T *)out,
-                    (const T *)v.s, h2, c->opts.omega, first_colour, zero, s,
-                    (last && dot) ? c->part : nullptr, 3 * (long long)c->pstride);
-                if (last && np > 0)
-                    c->dot_np = np;
-                two = true;
-            }
+        const bool two = sw + 2 <= nu && fused2_fits(v.d);
+        if (two) {
+            // the last pass may also form the outer loop's dot product
+            const bool last = sw + 2 == nu;
+            const int np = launch_rbgs_fused2<T>(
+                v.d, c->bc, b0, b1, b2, (const T *)v.r, (const T *)cur, (T *)out, (const T *)v.s, h2,
+                c->opts.omega, first_colour, zero, s, (last && dot) ? c->part : nullptr,
+                3 * (long long)c->pstride);
+            if (last && np > 0)
+                c->dot_np = np;
         }
         if (!two)
             launch_rbgs_fused<T>(v.d, c->bc, b0, b1, b2, (const T *)v.r, (const T *)cur, (T *)out,
@@ -782,7 +779,7 @@ void level_down(pp_ctx *c, Hier &H, int l, hipStream_t s, bool warm = false)
     LevelBuf &v = H.lev[l];
     const double h2 = v.h * v.h;
     const T *b0 = (const T *)v.b[0], *b1 = (const T *)v.b[1], *b2 = (const T *)v.b[2];
-    if (cells(v.d) > fused_min_cells<T>() && fused_plane_fits(v.d, sizeof(T))) {
+    if (fused_level<T>(v.d, c->opts.nu_pre)) {
         v.cur = warm ? fused_sweeps<T>(c, v, l, c->opts.nu_pre, v.cur, 0, false, s)
                      : fused_sweeps<T>(c, v, l, c->opts.nu_pre, v.e2, 0, true, s);
     } else {
@@ -813,7 +810,7 @@ void level_up(pp_ctx *c, Hier &H, int l, hipStream_t s)
         KT t(c, PP_KT_PROLONG, l == 0);
         launch_prolong<T>(v.d, c->bc, (const T *)H.lev[l + 1].cur, (T *)v.cur, c->pw[l], s);
     }
-    if (cells(v.d) > fused_min_cells<T>() && fused_plane_fits(v.d, sizeof(T))) {
+    if (fused_level<T>(v.d, c->opts.nu_post)) {
         v.cur = fused_sweeps<T>(c, v, l, c->opts.nu_post, v.cur, 1, false, s,
                                 l == 0 && c->dot_on);
     } else {
@@ -913,8 +910,7 @@ int capture_coarse(pp_ctx *c, Hier &H)
     if (!H.present || H.tail < 2)
         return PP_OK;             // levels 1 .. L-1 are one kernel or none
     prepare_fused<T>();
-    if constexpr (!std::is_same<T, double>::value)
-        prepare_fused2<T>();
+    prepare_fused2<T>();
     hipStream_t cap = nullptr;
     PP_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipGraph_t g = nullptr;

@@ -511,99 +511,119 @@ void launch_rbgs_fused(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
 }
 
 // ---------------------------------------------------------------------------
-// Two sweeps in one pass (FP32 arithmetic: FP32 and FP16 storage).
+// Two sweeps in one pass.
 //
 // The plane step above, extended by two phases that lag behind it.  At step k
 //   A: first colour of plane k, sweep 1 (from e_in, as above);
 //   B: second colour of plane k-1, sweep 1;
 //   C: first colour of plane k-2, sweep 2, from the finished sweep-1 values;
 //   D: second colour of plane k-3, sweep 2, which completes that plane.
-// Every phase reads its in-plane neighbours from an LDS plane written one
-// step earlier (A from the published inputs, B from A's values, C from B's,
-// D from C's) and its z neighbours, the same pair's cells in the planes above
-// and below, from registers.  C and D update the same cells as A and B two
-// steps before, so they reuse the coefficients, reciprocal diagonal and h^2 r
-// that A and B computed, carried in registers.  One barrier per step
-// separates A (and the publication of the next plane's inputs) from B, C and
-// D.  Each phase consumes one ring cell, so the ring around the tile is two
-// pairs wide and three rows deep, and a chunk of output planes [k0, k1) is
-// marched from k0-3 to k1+2.  Per cell the pass moves the bytes of one sweep.
+// Of a cell's six neighbours three are the thread's own: the other cell of its
+// pair and the same cell in the planes above and below, all in registers.  The
+// other three, the next pair's cell in x and the rows beside it, are read from
+// an LDS plane written one step earlier (A from the published inputs, B from
+// A's values, C from B's, D from C's).  Every such plane holds one value per
+// pair, since a phase reads the other colour only, so a wave reads consecutive
+// words.  C and D update the same cells as A and B two steps before, so they
+// reuse the coefficients, reciprocal diagonal and right-hand side of A and B,
+// carried in registers.  One barrier per step separates A (and the publication
+// of the next plane's inputs) from B, C and D.  Each phase consumes one ring
+// cell, so the ring around the tile is two pairs wide and three rows deep, and
+// a chunk of output planes [k0, k1) is marched from k0-3 to k1+2.  Per cell the
+// pass moves the bytes of one sweep.
 // ---------------------------------------------------------------------------
 constexpr int GTX = 64;                   // tile width in cells (32 pairs)
 constexpr int GTY = 8;                    // tile height in rows
 constexpr int GPX = GTX / 2 + 4;          // pairs per row: two ring pairs on each side
 constexpr int GRY = GTY + 6;              // rows: three ring rows on each side
 constexpr int GTHREADS = (GPX * GRY + 63) / 64 * 64;
-constexpr int GLW = GTX + 12;             // LDS row: cells i0-6 .. i0+GTX+5
-constexpr int GLR = GTY + 8;              // LDS rows: j0-4 .. j0+GTY+3
+constexpr int GLW = GPX + 2;              // LDS row: the pairs and one beyond on each side
+constexpr int GLR = GRY + 2;              // LDS rows: one beyond on each side
+
+// Whole-array buffer resources (FLAT) take a plane's byte offset in the 32-bit
+// address of each load: a missing plane is at an offset past every array, and
+// that offset plus OFF_NONE still does not wrap.  Arrays up to this size.
+constexpr unsigned FLAT_NONE = 0x7ffffff0u;
+inline bool fused2_flat(Dims d, size_t word) { return cells(d) * word <= FLAT_NONE; }
+
+// Planes of loads in flight beyond k+1: three for FP32; one for FP16 (whose
+// registers then allow two workgroups per CU) and for FP64 (two spill).
+template <typename T>
+struct Fused2Depth {
+    static constexpr int value = sizeof(T) == 4 ? 3 : 1;
+};
 
 // what phase A (B) computed for a cell, for phase C (D) two steps later
+template <typename C>
 struct GsLag {
-    float xl, xh, yl, yh, zl, zh;   // link coefficients
-    float inv;                      // om / diagonal, or 0 for an excluded cell or missing plane
-    float hr;                       // h^2 r
+    C xi, xo, yl, yh, zl, zh;       // link coefficients (xi: inside the pair, xo: beyond it)
+    C inv;                          // om / diagonal, or 0 for an excluded cell or missing plane
+    C r;                            // right-hand side (EXACT: h^2 r, rounded)
 };
+
+__device__ __forceinline__ float om_over(float om, float d) { return om * __builtin_amdgcn_rcpf(d); }
+__device__ __forceinline__ double om_over(double om, double d) { return om / d; }
 
 // om: the over-relaxation of eq. beta_pressure, folded into the reciprocal
 // diagonal that the lag registers carry (inv = om / diag), so every phase
 // forms e <- (1 - om) e + inv (sum - h^2 r); the old value of phases A and B
 // is e_in (0 in the ZERO pass), that of C and D the sweep-1 value.
-// DOT (FP32, regular pass): also the partial sums of r . e_out over each
+// DOT (FP32 and FP64 storage, regular pass): also the partial sums of r . e_out over each
 // workgroup's output cells, r the pass's own right-hand side, products summed
 // in FP64 (the outer iteration's residual against the preconditioned one,
-// both in units of the V-cycle's scale); part[workgroup].  The h^2 r values
-// that phases C and D already carry supply r, so nothing more is loaded.
-template <typename T, bool ZERO, bool SIG, bool DOT, bool WHOLE>
-__global__ __launch_bounds__(GTHREADS) void k_rbgs_fused2(Dims d, Bc bc, const T *__restrict__ bx,
-                                                          const T *__restrict__ by,
-                                                          const T *__restrict__ bz,
-                                                          const T *__restrict__ r,
-                                                          const T *__restrict__ ein,
-                                                          T *__restrict__ eout,
-                                                          const T *__restrict__ sg, float h2,
-                                                          float om, int c0, int kz, unsigned tx_tiles,
-                                                          unsigned ty_tiles,
-                                                          double *__restrict__ part)
+// both in units of the V-cycle's scale); part[workgroup].  The values of r that
+// phases C and D already carry supply it (as h^2 r), so nothing more is loaded.
+// FP16 storage sums x, y, z faces low before high (EXACT): its iterates
+// repeat only with every FP32 rounding, so which products are fused is spelt
+// out below.
+template <typename T, bool ZERO, bool SIG, bool DOT, bool WHOLE, bool FLAT>
+__global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused2(
+    Dims d, Bc bc, const T *__restrict__ bx, const T *__restrict__ by, const T *__restrict__ bz,
+    const T *__restrict__ r, const T *__restrict__ ein, T *__restrict__ eout,
+    const T *__restrict__ sg, typename Acc<T>::type h2, typename Acc<T>::type om, int c0, int kz,
+    unsigned tx_tiles, unsigned ty_tiles, double *__restrict__ part)
 {
-    using C = float;
+    using C = typename Acc<T>::type;
     using T2 = typename Vec2<T>::type;
-    // Planes of loads in flight beyond k+1: three for FP32, one for FP16
-    // (whose registers then allow two workgroups per CU).  The loop is
-    // unrolled by the buffer count FNB; with FP32's six buffers, a multiple
-    // of both slot periods (2 and 3), every LDS slot index is a compile-time
-    // constant.
-    constexpr int FPD = sizeof(T) == 4 ? 3 : 1;
+    constexpr bool EXACT = std::is_same<T, _Float16>::value;
+    // The loop is unrolled by the buffer count FNB, a multiple of both slot
+    // periods (2 and NRED), so every LDS slot index is a compile-time constant.
+    constexpr int FPD = Fused2Depth<T>::value;
     constexpr int FNB = FPD + 3;
-    constexpr bool CT_SLOTS = FNB % 6 == 0;
+    constexpr int NRED = FNB % 3 == 0 ? 3 : (FNB % 4 == 0 ? 4 : 5);
+    static_assert(FNB % 2 == 0 && FNB % NRED == 0, "slot periods");
     static_assert(!DOT || (!ZERO && !SIG), "the dot product rides on regular passes");
     const C om1 = C(1) - om;
-    __shared__ C SE[2][GLR][GLW];     // e_in of planes k, k+1
-    __shared__ C SX[2][GLR][GLW];     // beta_x of planes k, k+1
-    __shared__ C SY[2][GLR][GLW];     // beta_y of planes k, k+1
-    __shared__ C RED1[3][GLR][GLW];   // phase A values (sweep 1, first colour)
-    __shared__ C BLK1[2][GLR][GLW];   // phase B values (sweep 1, second colour)
-    __shared__ C RED2[2][GLR][GLW];   // phase C values (sweep 2, first colour)
+    __shared__ C SE[2][GLR * GLW];        // e_in of planes k, k+1: second colour
+    __shared__ C SX[2][GLR * GLW];        // beta_x of planes k, k+1: a pair's low face
+    __shared__ T2 SY[2][GLR * GLW];       // beta_y of planes k, k+1: both cells
+    __shared__ C RED1[NRED][GLR * GLW];   // phase A values (sweep 1, first colour)
+    __shared__ C BLK1[2][GLR * GLW];      // phase B values (sweep 1, second colour)
+    __shared__ C RED2[2][GLR * GLW];      // phase C values (sweep 2, first colour)
     int bxi, byi, bzi;
     xcd_tile(tx_tiles, ty_tiles, bxi, byi, bzi);
     const int i0 = bxi * GTX, j0 = byi * GTY;
     const int k0 = bzi * kz;
     const int k1 = min(k0 + kz, d.nz);
-    const int xend = min(i0 + GTX, d.nx), yend = min(j0 + GTY, d.ny);
+    const int yend = min(j0 + GTY, d.ny);
 
     const int tid = threadIdx.x;
     const bool in_layout = tid < GPX * GRY;
     const int tl = in_layout ? tid : 0;
-    const int pl = tl % GPX - 2;      // pair within the tile; -2, -1 and those past xend are ring
+    const int pl = tl % GPX;          // pair of the tile; the first two and the last two are ring
     const int rl = tl / GPX - 3;      // row within the tile; -3..-1 and those past yend are ring
     const int xu = i0 + 2 * pl, ju = j0 + rl;
     int x = xu, j = ju;
-    // ring pairs / rows past the grid's end wrap when periodic (at most two
-    // pairs, three rows); with walls they hold no cell
+    // A tile is read from i0 on, so that its rows start on a cache line, and
+    // owns the cells from i0 + 4 (with a wall at x = 0 the first tile owns from 0)
+    // to i0 + GTX + 3; along a periodic x the tiles own [4, nx + 4).  Pairs and
+    // rows past the grid's end wrap when periodic (ring: at most two pairs,
+    // three rows); with walls they hold no cell.
+    const int xlim = bc.x ? d.nx : d.nx + 4;          // end of the cells owned along x
+    const int xown = bc.x && i0 == 0 ? 0 : i0 + 4, xend = min(i0 + GTX + 4, xlim);
     bool act = in_layout;
-    if (xu < 0) {
-        if (bc.x) act = false; else x = xu + d.nx;
-    } else if (xu >= d.nx) {
-        if (bc.x || xu >= d.nx + 4) act = false; else x = xu - d.nx;
+    if (xu >= d.nx) {
+        if (bc.x || xu >= d.nx + 8) act = false; else x = xu - d.nx;
     }
     if (ju < 0) {
         if (bc.y) act = false; else j = ju + d.ny;
@@ -614,27 +634,25 @@ __global__ __launch_bounds__(GTHREADS) void k_rbgs_fused2(Dims d, Bc bc, const T
         x = 0;
         j = 0;
     }
-    const bool owned = act && pl >= 0 && xu < xend && rl >= 0 && ju < yend;
+    const bool owned = act && xu >= xown && xu < xend && rl >= 0 && ju < yend;
     const bool dn_row = act && rl == -3;              // publishes the row below it
     const bool up_row = act && ju == yend + 2;        // publishes the row above it
     const int jm = (j == 0) ? d.ny - 1 : j - 1;
     const int jp = (j == d.ny - 1) ? 0 : j + 1;
     const bool wyl = bc.y && j == 0, wyh = bc.y && j == d.ny - 1;
     const bool wxl = bc.x && x == 0;
-    const int jo = dn_row ? jm : (up_row ? jp : j);
-    const bool zo = up_row ? wyh : wyl;
+    const int jo = dn_row ? jm : jp;
     const bool beyond = dn_row || up_row;   // only these threads read the row beyond
     const unsigned oc0 = (unsigned)(((size_t)j * d.nx + x) * sizeof(T));
     const unsigned oo0 = (unsigned)(((size_t)jo * d.nx + x) * sizeof(T));
     const unsigned oc = act ? oc0 : OFF_NONE;
-    const unsigned oo = (act && beyond) ? oo0 : OFF_NONE;
+    const unsigned oo = beyond ? oo0 : OFF_NONE;
     const unsigned ocy = (act && !wyl) ? oc0 : OFF_NONE;
-    const unsigned ooy = (act && beyond && !zo) ? oo0 : OFF_NONE;
+    const unsigned ooy = (up_row && !wyh) ? oo0 : OFF_NONE;   // the row below has no face to lend
     const unsigned ost = owned ? oc0 : OFF_NONE;
     const unsigned pbytes = (unsigned)((size_t)d.nx * d.ny * sizeof(T));
-    const int lx = 2 * pl + 6;        // LDS column of the pair's first cell
-    const int ly = rl + 4;            // LDS row of the pair
-    const int lyo = dn_row ? ly - 1 : (up_row ? ly + 1 : ly);
+    const int li = (rl + 4) * GLW + pl + 1;          // LDS entry of the pair
+    const int lio = li + (dn_row ? -GLW : GLW);      // ... of the row beyond
 
     // plane q: its wrapped index, and whether it exists (walls end the grid);
     // selects rather than branches (q is within four planes of the grid)
@@ -645,171 +663,216 @@ __global__ __launch_bounds__(GTHREADS) void k_rbgs_fused2(Dims d, Bc bc, const T
         qw = ok ? qw : 0;
         return ok;
     };
+    const unsigned abytes = FLAT ? pbytes * (unsigned)d.nz : 0u;
+    const auto fe = plane_rsrc(ein, abytes), fr = plane_rsrc(r, abytes),
+               fbx = plane_rsrc(bx, abytes), fby = plane_rsrc(by, abytes),
+               fbz = plane_rsrc(bz, abytes), fsg = plane_rsrc(sg, abytes),
+               fo = plane_rsrc(eout, abytes);
     auto load_in = [&](int q, PairIn<T> &v) __attribute__((always_inline)) {
         int qw;
-        const unsigned nb = plane(q, qw) ? pbytes : 0u;
-        const size_t pb = (size_t)qw * pbytes;
-        auto rs = [&](const T *base, unsigned n) {
-            return plane_rsrc(reinterpret_cast<const char *>(base) + pb, n);
-        };
-        if (!ZERO) {
-            const auto re = rs(ein, nb);
-            v.e = ld_pair<T>(re, oc);
-            v.eo = ld_pair<T>(re, oo);
+        const bool ok = plane(q, qw);
+        const bool okz = ok && !(bc.z && qw == 0);   // the wall below plane 0
+        if constexpr (FLAT) {
+            const unsigned po = ok ? (unsigned)qw * pbytes : FLAT_NONE;
+            const unsigned poz = okz ? po : FLAT_NONE;
+            if (!ZERO) {
+                v.e = ld_pair<T>(fe, oc + po);
+                v.eo = ld_pair<T>(fe, oo + po);
+            }
+            v.r = ld_pair<T>(fr, oc + po);
+            v.bx = ld_pair<T>(fbx, oc + po);
+            v.by = ld_pair<T>(fby, ocy + po);
+            v.byo = ld_pair<T>(fby, ooy + po);
+            v.bz = ld_pair<T>(fbz, oc + poz);
+            if (SIG)
+                v.sg = ld_pair<T>(fsg, oc + po);
+        } else {
+            const unsigned nb = ok ? pbytes : 0u;
+            const size_t pb = (size_t)qw * pbytes;
+            auto rs = [&](const T *base, unsigned n) {
+                return plane_rsrc(reinterpret_cast<const char *>(base) + pb, n);
+            };
+            if (!ZERO) {
+                const auto re = rs(ein, nb);
+                v.e = ld_pair<T>(re, oc);
+                v.eo = ld_pair<T>(re, oo);
+            }
+            v.r = ld_pair<T>(rs(r, nb), oc);
+            v.bx = ld_pair<T>(rs(bx, nb), oc);
+            const auto ry = rs(by, nb);
+            v.by = ld_pair<T>(ry, ocy);
+            v.byo = ld_pair<T>(ry, ooy);
+            v.bz = ld_pair<T>(rs(bz, okz ? nb : 0u), oc);
+            if (SIG)
+                v.sg = ld_pair<T>(rs(sg, nb), oc);
         }
-        v.r = ld_pair<T>(rs(r, nb), oc);
-        v.bx = ld_pair<T>(rs(bx, nb), oc);
-        const auto ry = rs(by, nb);
-        v.by = ld_pair<T>(ry, ocy);
-        v.byo = ld_pair<T>(ry, ooy);
-        v.bz = ld_pair<T>(rs(bz, (bc.z && qw == 0) ? 0u : nb), oc);
-        if (SIG)
-            v.sg = ld_pair<T>(rs(sg, nb), oc);
+    };
+    auto store_out = [&](int q, T2 v) __attribute__((always_inline)) {
+        if constexpr (FLAT)
+            st_pair<T>(fo, ost + (unsigned)q * pbytes, v);
+        else
+            st_pair<T>(plane_rsrc(reinterpret_cast<const char *>(eout) + (size_t)q * pbytes, pbytes),
+                       ost, v);
     };
     auto pick = [](int o, T2 v) -> C { return C(o ? v.y : v.x); };
-    auto publish = [&](int slot, const PairIn<T> &v) __attribute__((always_inline)) {
+    // inputs of a plane whose first-colour cells are at offset o1 of this row
+    auto publish = [&](int slot, int o1, const PairIn<T> &v) __attribute__((always_inline)) {
         if (!act)
             return;
-        if (!ZERO) {
-            SE[slot][ly][lx] = C(v.e.x);
-            SE[slot][ly][lx + 1] = C(v.e.y);
-        }
-        SX[slot][ly][lx] = wxl ? C(0) : C(v.bx.x);
-        SX[slot][ly][lx + 1] = C(v.bx.y);
-        SY[slot][ly][lx] = C(v.by.x);
-        SY[slot][ly][lx + 1] = C(v.by.y);
+        if (!ZERO)
+            SE[slot][li] = pick(1 - o1, v.e);
+        SX[slot][li] = C(v.bx.x);
+        SY[slot][li] = v.by;
         if (beyond) {
-            if (!ZERO) {
-                SE[slot][lyo][lx] = C(v.eo.x);
-                SE[slot][lyo][lx + 1] = C(v.eo.y);
-            }
-            SY[slot][lyo][lx] = C(v.byo.x);
-            SY[slot][lyo][lx + 1] = C(v.byo.y);
+            if (!ZERO)
+                SE[slot][lio] = pick(o1, v.eo);
+            if (up_row)
+                SY[slot][lio] = v.byo;
         }
     };
 
-    for (int i = tid; i < 2 * GLR * GLW; i += GTHREADS) {
-        (&SE[0][0][0])[i] = C(0);
-        (&SX[0][0][0])[i] = C(0);
-        (&SY[0][0][0])[i] = C(0);
-        (&BLK1[0][0][0])[i] = C(0);
-        (&RED2[0][0][0])[i] = C(0);
+    for (int i = tid; i < GLR * GLW; i += GTHREADS) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            SE[q][i] = C(0);
+            SX[q][i] = C(0);
+            SY[q][i] = T2{T(0), T(0)};
+            BLK1[q][i] = C(0);
+            RED2[q][i] = C(0);
+        }
+#pragma unroll
+        for (int q = 0; q < NRED; ++q)
+            RED1[q][i] = C(0);
     }
-    for (int i = tid; i < 3 * GLR * GLW; i += GTHREADS)
-        (&RED1[0][0][0])[i] = C(0);
 
     // own-pair values of earlier planes: A's of k-1, k-2; B's of k-2, k-3;
     // C's of k-3, k-4
     C red_km1 = C(0), red_km2 = C(0);
     C blk_km1 = C(0), blk_km2 = C(0);
     C r2_km1 = C(0), r2_km2 = C(0);
-    C sxl = C(0), sxh = C(0), syl = C(0), syh = C(0);
-    GsLag a1{}, a2{}, b1{}, b2{};
-    // DOT: h^2 r of C's cell of the previous step (the first-colour cell of
-    // the plane phase D completes), and the sum of h^2 r e_out
-    C hrc = C(0);
+    // faces of the second-colour cell of plane k-1
+    C sxi = C(0), sxo = C(0), syl = C(0), syh = C(0);
+    GsLag<C> a1{}, a2{}, b1{}, b2{};
+    // DOT: r of C's cell of the previous step (the first-colour cell of the
+    // plane phase D completes), and the sum of h^2 r e_out
+    C rc = C(0);
     double dacc = 0.0;
 
     // LDS slots are counted from the first plane of the march, kb = k0 - 3:
     // plane k's inputs sit in slot (k - kb) mod 2, its phase-A values in slot
-    // (k - kb) mod 3; u is the unrolled step index, (k - kb) mod FNB
+    // (k - kb) mod NRED; u is the unrolled step index, (k - kb) mod FNB
     const int kb = k0 - 3;
     const int p0 = (c0 + j + kb) & 1;
+    // the next pair in x of a cell at offset p0 of its pair, and at the other
+    const int ladj[2] = {li + (p0 ? 1 : -1), li + (p0 ? -1 : 1)};
     // waves that hold only outer ring rows, whose phase C and D values no
     // thread reads, skip those phases
     const bool cdw = __any(in_layout && rl >= -1 && rl <= GTY);
+    // sum of the six links of a cell at offset o: own values ei (x) and zl, zh
+    // (z), the rest from LDS
+    auto links6 = [&](bool second, int o, C xi, C xo, C yl, C yh, C zl, C zh, C ei, C eo, C el,
+                      C eh, C fl, C fh) __attribute__((always_inline)) -> C {
+        C t;
+        if (EXACT) {
+            const C x0 = o ? xi : xo, x1 = o ? xo : xi;
+            const C e0 = o ? ei : eo, e1 = o ? eo : ei;
+            t = second ? fma(x1, e1, x0 * e0) : fma(x0, e0, x1 * e1);
+        } else {
+            t = fma(xo, eo, xi * ei);
+        }
+        t = fma(yl, el, t);
+        t = fma(yh, eh, t);
+        t = fma(zl, fl, t);
+        return fma(zh, fh, t);
+    };
+    auto minus_h2r = [&](C t, C rl) -> C { return EXACT ? t - rl : fma(-h2, rl, t); };
     auto step = [&](int k, int u, PairIn<T> &pm, PairIn<T> &pc, PairIn<T> &pn, PairIn<T> &pf)
                     __attribute__((always_inline)) {
-        load_in(k + 1 + FPD, pf);
-        const int st = CT_SLOTS ? u : k - kb;
-        const int si = st & 1;
-        const int s3 = CT_SLOTS ? u % 3 : slot3(st);
+        const int si = u & 1, s3 = u % NRED, sb = (u + NRED - 1) % NRED;
         int kw;
         const bool kin = act && plane(k, kw);
-        const int o = p0 ^ (st & 1);      // first-colour cell of the pair in plane k
-        const int ca = lx + o;            // the cell every phase of this step updates
+        const int o = p0 ^ si;            // first-colour cell of the pair in plane k
+        const int la = ladj[si];          // every phase of this step updates offset o
         // phase A: first colour of plane k, sweep 1
-        const C xl = SX[si][ly][ca], xh = SX[si][ly][ca + 1];
-        const C yl = SY[si][ly][ca], yh = SY[si][ly + 1][ca];
+        const C xr = SX[si][li + 1];
+        const T2 yu = SY[si][li + GLW];
+        const C xl = wxl ? C(0) : C(pc.bx.x);
+        const C xi = C(pc.bx.y), xo = o ? xr : xl, nxo = o ? xl : xr;
+        const C yl = pick(o, pc.by), nyl = pick(1 - o, pc.by);
+        const C yh = pick(o, yu), nyh = pick(1 - o, yu);
         const C zl = pick(o, pc.bz), zh = pick(o, pn.bz);
-        C diag = (xl + xh) + (yl + yh) + (zl + zh);
+        C diag = (xi + xo) + (yl + yh) + (zl + zh);
         if (SIG)
             diag += pick(o, pc.sg);
         C s = C(0);
         if (!ZERO)
-            s = xl * SE[si][ly][ca - 1] + xh * SE[si][ly][ca + 1] + yl * SE[si][ly - 1][ca] +
-                yh * SE[si][ly + 1][ca] + zl * pick(o, pm.e) + zh * pick(o, pn.e);
-        const C inva = (kin && diag > C(0)) ? om * __builtin_amdgcn_rcpf(diag) : C(0);
-        const C hra = h2 * pick(o, pc.r);
-        C red = (s - hra) * inva;
+            s = links6(false, o, xi, xo, yl, yh, zl, zh, pick(1 - o, pc.e), SE[si][la],
+                       SE[si][li - GLW], SE[si][li + GLW], pick(o, pm.e), pick(o, pn.e));
+        const C inva = (kin && diag > C(0)) ? om_over(om, diag) : C(0);
+        const C ra = pick(o, pc.r);
+        C red = fma(-h2, ra, s) * inva;
         if (!ZERO) {
-            red = om1 * pick(o, pc.e) + red;
+            red = fma(om1, pick(o, pc.e), red);
             if (SIG)
                 red = inva == C(0) ? C(0) : red;   // an excluded cell stays 0
         }
-        const int cb = lx + 1 - o;
-        const C nxl = SX[si][ly][cb], nxh = SX[si][ly][cb + 1];
-        const C nyl = SY[si][ly][cb], nyh = SY[si][ly + 1][cb];
         if (act)
-            RED1[s3][ly][ca] = red;
-        publish(si ^ 1, pn);
+            RED1[s3][li] = red;
+        publish(si ^ 1, 1 - o, pn);
+        load_in(k + 1 + FPD, pf);   // here the registers of phase A are free again
         __syncthreads();
         // The in-plane neighbours of phases B, C and D were all written before
         // this barrier (A's of plane k-1 in this step, B's of plane k-2 and C's
         // of plane k-3 in the previous one), and none is overwritten below, so
-        // all twelve LDS reads are issued at once.
-        const int sb = s3 == 0 ? 2 : s3 - 1;
-        const C bw = RED1[sb][ly][ca - 1], be = RED1[sb][ly][ca + 1];
-        const C bs = RED1[sb][ly - 1][ca], bn = RED1[sb][ly + 1][ca];
-        C cw = C(0), ce = C(0), cs = C(0), cn = C(0), dw = C(0), de = C(0), ds = C(0), dn = C(0);
+        // all nine LDS reads are issued at once.
+        const C bo = RED1[sb][la], bs = RED1[sb][li - GLW], bn = RED1[sb][li + GLW];
+        C co = C(0), cs = C(0), cn = C(0), dq = C(0), ds = C(0), dn = C(0);
         if (cdw) {
-            cw = BLK1[si][ly][ca - 1];
-            ce = BLK1[si][ly][ca + 1];
-            cs = BLK1[si][ly - 1][ca];
-            cn = BLK1[si][ly + 1][ca];
-            dw = RED2[si ^ 1][ly][ca - 1];
-            de = RED2[si ^ 1][ly][ca + 1];
-            ds = RED2[si ^ 1][ly - 1][ca];
-            dn = RED2[si ^ 1][ly + 1][ca];
+            co = BLK1[si][la];
+            cs = BLK1[si][li - GLW];
+            cn = BLK1[si][li + GLW];
+            dq = RED2[si ^ 1][la];
+            ds = RED2[si ^ 1][li - GLW];
+            dn = RED2[si ^ 1][li + GLW];
         }
         // phase B: second colour of plane k-1, sweep 1
         const C bzl = pick(o, pm.bz), bzh = pick(o, pc.bz);
-        C dg = (sxl + sxh) + (syl + syh) + (bzl + bzh);
+        C dg = (sxi + sxo) + (syl + syh) + (bzl + bzh);
         if (SIG)
             dg += pick(o, pm.sg);
-        const C invb = dg > C(0) ? om * __builtin_amdgcn_rcpf(dg) : C(0);
-        const C hrb = h2 * pick(o, pm.r);
-        C blk = (sxl * bw + sxh * be + syl * bs + syh * bn + bzl * red_km2 + bzh * red - hrb) * invb;
+        const C invb = dg > C(0) ? om_over(om, dg) : C(0);
+        const C rb = pick(o, pm.r);
+        C blk = fma(-h2, rb,
+                    links6(false, o, sxi, sxo, syl, syh, bzl, bzh, red_km1, bo, bs, bn, red_km2, red)) *
+                invb;
         if (!ZERO) {
-            blk = om1 * pick(o, pm.e) + blk;
+            blk = fma(om1, pick(o, pm.e), blk);
             if (SIG)
                 blk = invb == C(0) ? C(0) : blk;
         }
         if (act)
-            BLK1[si ^ 1][ly][ca] = blk;
+            BLK1[si ^ 1][li] = blk;
         C red2 = C(0);
         if (cdw) {
             // phase C: first colour of plane k-2, sweep 2 (A's cell of step k-2)
-            red2 = om1 * red_km2 + (a2.xl * cw + a2.xh * ce + a2.yl * cs + a2.yh * cn +
-                                    a2.zl * blk_km2 + a2.zh * blk - a2.hr) *
-                                       a2.inv;
+            red2 = links6(true, o, a2.xi, a2.xo, a2.yl, a2.yh, a2.zl, a2.zh, blk_km1, co, cs, cn, blk_km2,
+                          blk);
+            red2 = fma(om1, red_km2, minus_h2r(red2, a2.r) * a2.inv);
             if (act)
-                RED2[si][ly][ca] = red2;
+                RED2[si][li] = red2;
             // phase D: second colour of plane k-3, sweep 2 (B's cell of step k-2)
-            const C blk2 = om1 * blk_km2 + (b2.xl * dw + b2.xh * de + b2.yl * ds + b2.yh * dn +
-                                            b2.zl * r2_km2 + b2.zh * red2 - b2.hr) *
-                                               b2.inv;
+            C blk2 = links6(true, o, b2.xi, b2.xo, b2.yl, b2.yh, b2.zl, b2.zh, r2_km1, dq, ds, dn, r2_km2,
+                            red2);
+            blk2 = fma(om1, blk_km2, minus_h2r(blk2, b2.r) * b2.inv);
             const int kd = k - 3;
             if (kd >= k0 && kd < k1) {
                 T2 outv;
                 outv.x = static_cast<T>(o ? r2_km1 : blk2);
                 outv.y = static_cast<T>(o ? blk2 : r2_km1);
-                st_pair<T>(
-                    plane_rsrc(reinterpret_cast<const char *>(eout) + (size_t)kd * pbytes, pbytes),
-                    ost, outv);
+                store_out(kd, outv);
                 if (DOT && owned)
-                    dacc += static_cast<double>(hrc) * static_cast<double>(r2_km1) +
-                            static_cast<double>(b2.hr) * static_cast<double>(blk2);
+                    dacc += static_cast<double>(h2 * rc) * static_cast<double>(r2_km1) +
+                            static_cast<double>(h2 * b2.r) * static_cast<double>(blk2);
             }
         }
         red_km2 = red_km1;
@@ -819,13 +882,13 @@ __global__ __launch_bounds__(GTHREADS) void k_rbgs_fused2(Dims d, Bc bc, const T
         r2_km2 = r2_km1;
         r2_km1 = red2;
         if (DOT)
-            hrc = a2.hr;
+            rc = a2.r;
         a2 = a1;
-        a1 = GsLag{xl, xh, yl, yh, zl, zh, inva, hra};
+        a1 = GsLag<C>{xi, xo, yl, yh, zl, zh, inva, EXACT ? h2 * ra : ra};
         b2 = b1;
-        b1 = GsLag{sxl, sxh, syl, syh, bzl, bzh, invb, hrb};
-        sxl = nxl;
-        sxh = nxh;
+        b1 = GsLag<C>{sxi, sxo, syl, syh, bzl, bzh, invb, EXACT ? h2 * rb : rb};
+        sxi = xi;
+        sxo = nxo;
         syl = nyl;
         syh = nyh;
     };
@@ -835,13 +898,11 @@ __global__ __launch_bounds__(GTHREADS) void k_rbgs_fused2(Dims d, Bc bc, const T
     for (int u = 0; u < FNB - 1; ++u)
         load_in(k0 - 4 + u, buf[u]);
     __syncthreads();                  // the zero fill is complete
-    publish(0, buf[1]);
+    publish(0, p0, buf[1]);
     __syncthreads();
     if constexpr (WHOLE) {
         // whole blocks of FNB steps, the last up to FNB - 1 steps past k1 + 2
-        // (they store nothing), as in the single sweep.  FP16 does not take
-        // this form: its registers would then allow one workgroup per CU
-        // instead of two.
+        // (they store nothing), as in the single sweep
         for (int k = kb; k <= k1 + 2; k += FNB) {
 #pragma unroll
             for (int u = 0; u < FNB; ++u)
@@ -889,9 +950,9 @@ static long long fused2_slots()
         dev = 0;
     if (cached[dev] == 0) {
         int per_cu = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu,
-                                                         k_rbgs_fused2<T, ZERO, SIG, DOT, false>,
-                                                         GTHREADS, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, k_rbgs_fused2<T, ZERO, SIG, DOT, !std::is_same<T, float>::value, true>,
+                GTHREADS, 0) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -909,7 +970,7 @@ void prepare_fused2()
     (void)fused2_slots<T, false, false, false>();
     (void)fused2_slots<T, true, true, false>();
     (void)fused2_slots<T, false, true, false>();
-    if constexpr (std::is_same<T, float>::value)
+    if constexpr (!std::is_same<T, _Float16>::value)
         (void)fused2_slots<T, false, false, true>();
 }
 
@@ -918,12 +979,17 @@ int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
                        const T *ein, T *eout, const T *sg, double h2, double omega,
                        int first_colour, bool zero, hipStream_t s, double *part, long long max_parts)
 {
-    const unsigned tx = (d.nx + GTX - 1) / GTX, ty = (d.ny + GTY - 1) / GTY;
-    // the fused dot product: FP32 regular passes without a diagonal term
-    const bool dot = part && std::is_same<T, float>::value && !zero && !sg;
+    using C = typename Acc<T>::type;
+    // the first tile of a row with walls owns four cells more (see the kernel)
+    const unsigned tx = bc.x ? (d.nx > GTX + 4 ? (d.nx - 4 + GTX - 1) / GTX : 1) : (d.nx + GTX - 1) / GTX;
+    const unsigned ty = (d.ny + GTY - 1) / GTY;
+    // the fused dot product: regular passes without a diagonal term (FP16
+    // storage keeps the sum of its own kernel)
+    constexpr bool MAY = !std::is_same<T, _Float16>::value;
+    const bool dot = MAY && part && !zero && !sg;
     long long slots;
     if (dot)
-        slots = fused2_slots<T, false, false, std::is_same<T, float>::value>();
+        slots = fused2_slots<T, false, false, MAY>();
     else
         slots = sg ? (zero ? fused2_slots<T, true, true, false>()
                            : fused2_slots<T, false, true, false>())
@@ -935,48 +1001,54 @@ int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
     const int kz = chunk_planes(d.nz, tiles, slots, 6, 2, dot ? max_parts / tiles : d.nz);
     const unsigned tz = (d.nz + kz - 1) / kz;
     const dim3 grid(tx * ty, tz);
-    // a chunk marches kz + 6 steps; FP16 keeps the exit after every step
-    const bool whole = std::is_same<T, float>::value && kz + 6 >= WHOLE_MIN_STEPS;
-#define PP_FUSED2_LAUNCH(Z, S, D)                                                              \
-    do {                                                                                       \
-        if (whole)                                                                             \
-            PP_LAUNCH((k_rbgs_fused2<T, Z, S, D, std::is_same<T, float>::value>), grid,        \
-                      dim3(GTHREADS), 0, s, d, bc, bx, by, bz, r, ein, eout, sg, (float)h2,    \
-                      (float)omega, first_colour, kz, tx, ty, part);                           \
-        else                                                                                   \
-            PP_LAUNCH((k_rbgs_fused2<T, Z, S, D, false>), grid, dim3(GTHREADS), 0, s, d, bc,   \
-                      bx, by, bz, r, ein, eout, sg, (float)h2, (float)omega, first_colour, kz, \
-                      tx, ty, part);                                                           \
-    } while (0)
+    // A chunk marches kz + 6 steps.  FP32 runs short ones with an exit after
+    // every step (whole blocks of six would march 12 steps for 8); FP16 and FP64
+    // always run whole blocks, of four: the other form's registers spill.
+    constexpr bool SHORT = std::is_same<T, float>::value;
+    const bool whole = !SHORT || kz + 6 >= WHOLE_MIN_STEPS;
+    auto go = [&](auto kern) {
+        PP_LAUNCH(kern, grid, dim3(GTHREADS), 0, s, d, bc, bx, by, bz, r, ein, eout, sg, (C)h2,
+                  (C)omega, first_colour, kz, tx, ty, part);
+    };
+    auto form = [&](auto z, auto g, auto dt) {
+        constexpr bool Z = decltype(z)::value, G = decltype(g)::value, DT = decltype(dt)::value;
+        if (!fused2_flat(d, sizeof(T)))
+            go(k_rbgs_fused2<T, Z, G, DT, true, false>);
+        else if (whole)
+            go(k_rbgs_fused2<T, Z, G, DT, true, true>);
+        else
+            go(k_rbgs_fused2<T, Z, G, DT, !SHORT, true>);
+    };
+    constexpr std::true_type Y{};
+    constexpr std::false_type N{};
     if (dot) {
-        if constexpr (std::is_same<T, float>::value)
-            PP_FUSED2_LAUNCH(false, false, true);
+        if constexpr (MAY)
+            form(N, N, Y);
         return (int)(grid.x * grid.y);
     }
     if (sg) {
         if (zero)
-            PP_FUSED2_LAUNCH(true, true, false);
+            form(Y, Y, N);
         else
-            PP_FUSED2_LAUNCH(false, true, false);
+            form(N, Y, N);
     } else {
         if (zero)
-            PP_FUSED2_LAUNCH(true, false, false);
+            form(Y, N, N);
         else
-            PP_FUSED2_LAUNCH(false, false, false);
+            form(N, N, N);
     }
-#undef PP_FUSED2_LAUNCH
     return 0;
 }
 
-template void prepare_fused2<float>();
-template void prepare_fused2<_Float16>();
-template int launch_rbgs_fused2<float>(Dims, Bc, const float *, const float *, const float *,
-                                       const float *, const float *, float *, const float *, double,
-                                       double, int, bool, hipStream_t, double *, long long);
-template int launch_rbgs_fused2<_Float16>(Dims, Bc, const _Float16 *, const _Float16 *,
-                                          const _Float16 *, const _Float16 *, const _Float16 *,
-                                          _Float16 *, const _Float16 *, double, double, int, bool,
-                                          hipStream_t, double *, long long);
+#define PP_INSTANTIATE_FUSED2(T)                                                                 \
+    template void prepare_fused2<T>();                                                          \
+    template int launch_rbgs_fused2<T>(Dims, Bc, const T *, const T *, const T *, const T *,    \
+                                       const T *, T *, const T *, double, double, int, bool,     \
+                                       hipStream_t, double *, long long);
+
+PP_INSTANTIATE_FUSED2(double)
+PP_INSTANTIATE_FUSED2(float)
+PP_INSTANTIATE_FUSED2(_Float16)
 
 #define PP_INSTANTIATE_FUSED(T)                                                                  \
     template void prepare_fused<T>();                                                           \

@@ -58,14 +58,11 @@ __host__ __device__ inline size_t cells(Dims d) { return (size_t)d.nx * d.ny * d
 constexpr int TAIL_MAX = 8;
 constexpr size_t TAIL_CELLS = 4096;       // a level joins the tail at or below this size
 constexpr int TAIL_STATE = 4096 + 2 * 512;   // doubles a split tail keeps between its launches
-constexpr size_t FUSED_MIN_CELLS = (size_t)1 << 18;   // fused sweeps above 64^3 cells
-// FP32 / FP16 storage, whose fused pass does two sweeps per launch, from 32^3 cells
+// Smoother of a level above the tail: fused sweeps from this many cells (on
+// smaller levels a launch per colour; the single sweep in FP64 only from
+// above 64^3, as an odd sweep count or a side under 8 cells needs it).
+constexpr size_t FUSED_MIN_CELLS = (size_t)1 << 18;
 constexpr size_t FUSED2_MIN_CELLS = (size_t)1 << 14;
-template <typename T>
-constexpr size_t fused_min_cells()
-{
-    return sizeof(T) == 8 ? FUSED_MIN_CELLS : FUSED2_MIN_CELLS;
-}
 
 // The fused sweep addresses a plane through 32-bit byte offsets with one
 // reserved out-of-range value: planes must stay below 2^31 bytes.
@@ -216,11 +213,11 @@ template <typename T>
 void launch_rbgs_fused(Dims d, Bc bc, const T *bx, const T *by, const T *bz, const T *r,
                        const T *ein, T *eout, const T *sg, double h2, double omega,
                        int first_colour, bool zero, hipStream_t s);
-// Two sweeps in one pass (FP32 and FP16 storage only), out of place, ein and
-// eout distinct; needs nz >= 8 (the chunks read four planes beyond their ends).
+// Two sweeps in one pass, out of place, ein and eout distinct; needs nz >= 8
+// (the chunks read four planes beyond their ends).
 template <typename T>
 void prepare_fused2();
-// With part given, an FP32 regular pass without sigma also writes the partial
+// With part given, an FP32 or FP64 regular pass without sigma also writes the partial
 // sums of r . e_out (its own right-hand side against its output, products in
 // FP64), one per workgroup, and returns their number (at most max_parts, which
 // must be at least the number of its x-y tiles); otherwise returns 0.
@@ -230,6 +227,15 @@ int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
                        int first_colour, bool zero, hipStream_t s, double *part = nullptr,
                        long long max_parts = 0);
 inline bool fused2_fits(Dims d) { return d.nz >= 8 && d.nx >= 8 && d.ny >= 8; }
+// whether nu sweeps of a level run fused
+template <typename T>
+bool fused_level(Dims d, int nu)
+{
+    if (!fused_plane_fits(d, sizeof(T)))
+        return false;
+    return cells(d) > FUSED_MIN_CELLS ||
+           (cells(d) > FUSED2_MIN_CELLS && (sizeof(T) < 8 || (fused2_fits(d) && nu % 2 == 0)));
+}
 template <typename T>
 void launch_resid_restrict(Dims fd, Bc bc, const T *bx, const T *by, const T *bz, const T *e,
                            const T *r, const T *sg, T *rH, double ih2, hipStream_t s);

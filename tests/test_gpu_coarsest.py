@@ -89,8 +89,9 @@ def test_general_operator(S, n):
 TAILS = [(16, 16, 16), (8, 8, 8), (10, 12, 8), (12, 10, 16), (24, 16, 8), (8, 8, 64)]
 
 
-def reference_vcycle(S, beta, bc, h, r, nu, omega):
-    """The same cycle from the single-kernel entry points, whose parity with
+def reference_vcycle(S, beta, bc, h, r, nu, omega, nu_fine=None):
+    """The same cycle (nu sweeps on levels of at most 4096 cells, nu_fine on
+    larger ones) from the single-kernel entry points, whose parity with
     the oracle is tested on its own, and numpy's pseudo-inverse."""
     shape = beta[0].shape
     n = shape[::-1]
@@ -101,15 +102,16 @@ def reference_vcycle(S, beta, bc, h, r, nu, omega):
         P = np.linalg.pinv(A, rcond=1e-12, hermitian=True)
         return dev((P @ r.cpu().numpy().reshape(-1)).reshape(shape)), A.shape[0] * kappa
     e = torch.zeros_like(r)
-    S.k_smooth(shape, h, bc, beta, r, e, sweeps=nu, zero_init=True, omega=omega)
+    sweeps = nu if int(np.prod(shape)) <= 4096 else nu_fine
+    S.k_smooth(shape, h, bc, beta, r, e, sweeps=sweeps, zero_init=True, omega=omega)
     half = tuple(v // 2 for v in shape)
     rH = torch.empty(half, dtype=torch.float64, device="cuda")
     S.k_resid_restrict(shape, h, bc, beta, e, r, rH)
     bH = tuple(torch.empty_like(rH) for _ in range(3))
     S.k_coarsen_beta(shape, h, bc, beta, bH)
-    eH, amp = reference_vcycle(S, bH, bc, 2 * h, rH, nu, omega)
+    eH, amp = reference_vcycle(S, bH, bc, 2 * h, rH, nu, omega, nu_fine)
     S.k_prolong_add_weighted(shape, h, bc, eH, S.k_prolong_weights(shape, h, bc, beta), e)
-    for _ in range(nu):
+    for _ in range(sweeps):
         out = torch.empty_like(e)
         S.k_smooth_fused(shape, h, bc, beta, r, e, out, first_colour=1, omega=omega)
         e = out
@@ -142,3 +144,58 @@ def test_tail_cycle(S, n, bc, precision):
     err = ((got - want).abs().max() / want.abs().max()).item()
     print(n, bc, precision, "err %.1e bound %.1e" % (err, bound), flush=True)
     assert err <= bound
+
+
+# Levels above the tail, smoothed by the two-sweep pass in every storage type:
+# several tiles of 64 x 8 cells and chunks of planes, rows that end inside a
+# tile, at its edge, and within the four cells that a tile owns beyond it
+# (nx = 68: one tile with walls, two when periodic), three sweeps (a pass and
+# a single sweep), sides of one tile.
+FUSED = [((32, 32, 32), 2), ((64, 24, 16), 2), ((68, 36, 20), 2), ((132, 20, 24), 2),
+         ((136, 16, 24), 3), ((72, 40, 48), 2)]
+
+
+@pytest.mark.parametrize("n,nu", FUSED)
+@pytest.mark.parametrize("bc", [(0, 0, 0), (1, 1, 1), (1, 0, 0), (0, 1, 1)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_fused_levels(S, n, nu, bc, precision):
+    shape = (n[2], n[1], n[0])
+    rng = np.random.default_rng(6)
+    beta = [10.0 ** rng.uniform(-1.0, 0.0, shape) for _ in range(3)]
+    for m in range(3):
+        if bc[m]:
+            np.moveaxis(beta[m], 2 - m, 0)[0] = 0.0
+    r = rng.uniform(-1.0, 1.0, shape)
+    beta, r = [dev(b) for b in beta], dev(r - r.mean())
+    h, omega = 0.125, 1.2
+    want, amp = reference_vcycle(S, beta, bc, h, r, 4, omega, nu)
+    with S.Solver(beta, h, bc, precision=precision, nu_pre=nu, nu_post=nu, omega=omega) as sol:
+        got = sol.vcycle(r)
+    eps = 2.0 ** -53 if precision == "fp64" else 2.0 ** -24     # as test_tail_cycle
+    bound = 600 * eps + amp * (2.0 ** -53 if precision == "fp64" else 2.0 ** -40)
+    err = ((got - want).abs().max() / want.abs().max()).item()
+    print(n, bc, precision, "err %.1e bound %.1e" % (err, bound), flush=True)
+    assert err <= bound
+
+
+@pytest.mark.parametrize("zero", [False, True])
+def test_two_sweep_pass_beyond_2_gib(S, zero):
+    """Arrays past the reach of a 32-bit byte offset: data that repeat every 40
+    planes give what the 40 planes alone give, to the rounding of the four
+    colour updates (which products are fused depends on a plane's place in the
+    march): 4 eps of the largest value each."""
+    nx, ny, per, rep = 1024, 1024, 40, 13                       # 2.18 GB an array
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    small = [torch.rand((per, ny, nx), generator=g, device="cuda") for _ in range(5)]
+    big = [t.repeat(rep, 1, 1) for t in small]
+    outs = []
+    for a in (small, big):
+        out = torch.empty_like(a[0])
+        S.k_smooth2_fused_f32(tuple(out.shape), 0.1, (1, 0, 0), a[:3], a[3], a[4], out,
+                              zero_init=zero, omega=1.2)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert big[0].numel() * 4 > 2 ** 31
+    diff = max((o - outs[0]).abs().max().item() for o in outs[1].view(rep, per, ny, nx))
+    assert diff <= 4 * 4 * 2.0 ** -24 * outs[0].abs().max().item()
