@@ -531,6 +531,17 @@ void launch_rbgs_fused(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
 // cell, so the ring around the tile is two pairs wide and three rows deep, and
 // a chunk of output planes [k0, k1) is marched from k0-3 to k1+2.  Per cell the
 // pass moves the bytes of one sweep.
+//
+// What bounds it (256^3 FP32, one workgroup per CU): the loads of a march with
+// the arithmetic taken out take 121 of its 130 us when a tile's rows start 16
+// bytes before a cache line, whatever the number of planes in flight (1 to 9):
+// a CU holds no more lines on their way than its L1, and a row of 72 cells
+// then touches four lines for 2.25.  Rows therefore start on a line (three);
+// the arithmetic alone takes 80 us.  Measured, regular / zero start: 256^3 FP32
+// 133 / 105 -> 120 / 101 us (512^3 1006 / 784 -> 877 / 730), FP16 storage 95 / 93
+// -> 80 / 85; FP64 in this form, with r.z, 191 / 175, where two single sweeps
+// take 335 / 323 and the dot product 47; at 64^3 FP64 10.6 / 10.1, where a
+// launch per colour takes 8 x 5 for two sweeps on each side.
 // ---------------------------------------------------------------------------
 constexpr int GTX = 64;                   // tile width in cells (32 pairs)
 constexpr int GTY = 8;                    // tile height in rows
