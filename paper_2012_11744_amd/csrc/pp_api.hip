@@ -768,10 +768,9 @@ void *fused_sweeps(pp_ctx *c, LevelBuf &v, int l, int nu, void *cur, int first_c
 }
 
 // nu_pre red-black sweeps (red first) from e = 0 on level l, then residual +
-// restriction into the right-hand side of level l + 1.  Large levels use the
-// fused out-of-place sweep (ping-pong between e and e2); smaller ones, where
-// the fused kernel's march along z is latency-bound, use one launch per
-// colour in place.  warm: the sweeps start from the level's current
+// restriction into the right-hand side of level l + 1.  The fused out-of-place
+// sweeps (ping-pong between e and e2) where fused_level says so, else one
+// launch per colour in place.  warm: the sweeps start from the level's current
 // correction (the second coarse correction of a W-cycle).
 template <typename T>
 void level_down(pp_ctx *c, Hier &H, int l, hipStream_t s, bool warm = false)

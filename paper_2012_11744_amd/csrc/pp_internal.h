@@ -58,9 +58,13 @@ __host__ __device__ inline size_t cells(Dims d) { return (size_t)d.nx * d.ny * d
 constexpr int TAIL_MAX = 8;
 constexpr size_t TAIL_CELLS = 4096;       // a level joins the tail at or below this size
 constexpr int TAIL_STATE = 4096 + 2 * 512;   // doubles a split tail keeps between its launches
-// Smoother of a level above the tail: fused sweeps from this many cells (on
-// smaller levels a launch per colour; the single sweep in FP64 only from
-// above 64^3, as an odd sweep count or a side under 8 cells needs it).
+// Smoother of a level above the tail.  Two-sweep passes run on every level
+// (24 x 20 x 28 cells, two sweeps on each side of the coarse correction: 18 us
+// in FP32, where a launch per colour takes 8 x 4.2 and their gaps); in FP16
+// storage above FUSED2_MIN_CELLS, as below that its iterates repeat only with
+// the launches per colour, which divide where the pass multiplies by a
+// reciprocal.  Single fused sweeps (an odd count, a side under 8 cells) run
+// above FUSED2_MIN_CELLS in FP32 and FP16, above FUSED_MIN_CELLS in FP64.
 constexpr size_t FUSED_MIN_CELLS = (size_t)1 << 18;
 constexpr size_t FUSED2_MIN_CELLS = (size_t)1 << 14;
 
@@ -233,8 +237,10 @@ bool fused_level(Dims d, int nu)
 {
     if (!fused_plane_fits(d, sizeof(T)))
         return false;
-    return cells(d) > FUSED_MIN_CELLS ||
-           (cells(d) > FUSED2_MIN_CELLS && (sizeof(T) < 8 || (fused2_fits(d) && nu % 2 == 0)));
+    const bool two = fused2_fits(d) && nu >= 2;
+    if (sizeof(T) == 8)
+        return cells(d) > FUSED_MIN_CELLS || (two && nu % 2 == 0);
+    return cells(d) > FUSED2_MIN_CELLS || (sizeof(T) == 4 && two);
 }
 template <typename T>
 void launch_resid_restrict(Dims fd, Bc bc, const T *bx, const T *by, const T *bz, const T *e,

@@ -151,7 +151,7 @@ def test_tail_cycle(S, n, bc, precision):
 # tile, at its edge, and within the four cells that a tile owns beyond it
 # (nx = 68: one tile with walls, two when periodic), three sweeps (a pass and
 # a single sweep), sides of one tile.
-FUSED = [((32, 32, 32), 2), ((64, 24, 16), 2), ((68, 36, 20), 2), ((132, 20, 24), 2),
+FUSED = [((32, 32, 32), 2), ((24, 20, 28), 2), ((36, 20, 8), 2), ((64, 24, 16), 2), ((68, 36, 20), 2), ((132, 20, 24), 2),
          ((136, 16, 24), 3), ((72, 40, 48), 2)]
 
 
