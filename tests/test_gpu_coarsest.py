@@ -83,6 +83,31 @@ def test_general_operator(S, n):
     check(S, beta, sigma, bc, 0.5, True)
 
 
+# (nx, ny, nz), walls: levels above one tile whose cells have two colours (every
+# periodic extent even), with a half-size matrix of 40 cells, 62 (of 125), one
+# tile exactly, 75 and 130
+COLOURS = [((4, 4, 5), (0, 0, 1)), ((5, 5, 5), (1, 1, 1)), ((4, 4, 8), (0, 0, 0)),
+           ((5, 5, 6), (1, 1, 0)), ((4, 5, 13), (0, 1, 1))]
+
+
+@pytest.mark.parametrize("n,bc", COLOURS)
+def test_two_colours(S, n, bc):
+    shape = (n[2], n[1], n[0])
+    rng = np.random.default_rng(5)
+    beta = [10.0 ** rng.uniform(-1.0, 0.0, shape) for _ in range(3)]
+    for m in range(3):
+        if bc[m]:
+            np.moveaxis(beta[m], 2 - m, 0)[0] = 0.0
+    check(S, beta, rng.uniform(0.0, 3.0, shape) * (rng.random(shape) < 0.5), bc, 0.5, True)
+    check(S, beta, None, bc, 0.125, False)
+    # excluded cells of both colours under the singular operator
+    hole = np.zeros(shape, dtype=bool)
+    hole.reshape(-1)[[5, 6, 20]] = True
+    for m in range(3):
+        beta[m][hole | np.roll(hole, 1, 2 - m)] = 0.0
+    check(S, beta, None, bc, 0.125, True)
+
+
 # (nx, ny, nz): grids that are whole tails of the V-cycle: 16^3 smooths two
 # levels; the others one, over a coarsest level of 64 (staged in LDS), 120, 240,
 # 384 and 512 cells (the last three solved by a kernel of their own)
