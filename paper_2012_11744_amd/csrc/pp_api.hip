@@ -1073,6 +1073,7 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
     c->scale_queued = false;
     bool first = true;
     D *dold = (D *)c->d64, *dnew = (D *)c->d64b;
+    double *dpart = c->part + 3 * c->pstride;   // pp_step's rows: its side stream is done by now
     int since = 0;
     double window = S.rel;
     // Iterations are launched ahead of the host's convergence test while the
@@ -1081,6 +1082,14 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
     // them in one iteration late, so the GPU does not idle during the test.
     int launched = 0, seen = 0;
     double rate = 0.0;   // residual reduction of the last folded iteration (0: none yet)
+    // sums that their consumer does not add up itself
+    auto settle = [&](FoldIn &in, size_t blocks, size_t n) {
+        if (!folds(c->d, blocks, n)) {
+            launch_finalize(in.part, in.pstride, in.n, in.op, 0, (double)c->N, first ? 1 : 0,
+                            c->scal, s);
+            in.n = 0;
+        }
+    };
     auto launch_iteration = [&]() -> int {
         // r . z comes from the V-cycle's last fine-level pass where that pass
         // can form it, else from its own kernel
@@ -1097,7 +1106,8 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
             nrz = np;
             op = OP_RZ;
         }
-        launch_finalize(c->part, c->pstride, nrz, op, 0, (double)c->N, first ? 1 : 0, c->scal, s);
+        FoldIn rz{c->part, nrz, c->pstride, op, c->scal};
+        settle(rz, dir_blocks<T>(c->d, x), nrz);
         int npd;
         {
             KT t(c, PP_KT_OUTER_APPLY, true);
@@ -1109,14 +1119,15 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
                 PP_TRY(ensure_b64(c));
             npd = launch_dir_apply<T>(c->d, c->bc, c->chain[0][0], c->chain[0][1], c->chain[0][2],
                                       op_rho(c), (const T *)v0.cur, dold, dnew, c->q64, x,
-                                      c->sig_on ? c->sig[0] : nullptr, c->scal, mode, ih2, c->part,
-                                      c->pstride, s);
+                                      c->sig_on ? c->sig[0] : nullptr, c->scal, mode, ih2, dpart,
+                                      c->pstride, rz, s);
         }
         first = false;
-        launch_finalize(c->part, c->pstride, npd, OP_ALPHA, 0, (double)c->N, 0, c->scal, s);
+        FoldIn dq{dpart, npd, c->pstride, OP_ALPHA, c->scal};
+        settle(dq, np, 2 * (size_t)npd);
         {
             KT t(c, PP_KT_OUTER_UPDATE, true);
-            launch_pcg_update<T>(c->d, c->q64, c->r64, (T *)v0.r, c->scal, c->part, s);
+            launch_pcg_update<T>(c->d, c->q64, c->r64, (T *)v0.r, c->scal, c->part, dq, s);
         }
         std::swap(dold, dnew);
         // the finalising kernel also writes the iteration's scalars to their
@@ -1568,7 +1579,7 @@ int setup_impl(const pp_grid *grid, const double *bx, const double *by, const do
         rc = dev_alloc_t(c, &c->q64, sizeof(double) * c->N);
     c->pstride = partials_max(c->d);
     if (rc == PP_OK)
-        rc = dev_alloc_t(c, &c->part, sizeof(double) * 6 * c->pstride);   // rows 3..5: pp_step's side stream
+        rc = dev_alloc_t(c, &c->part, sizeof(double) * 6 * c->pstride);   // rows 3..5: pp_step's side stream, the direction pass
     if (rc == PP_OK)
         rc = dev_alloc_t(c, &c->scal, sizeof(double) * S_NSLOTS);
     if (rc != PP_OK)

@@ -163,7 +163,7 @@ enum Slot {
     S_MEAN = 0,     // mean of the right-hand side
     S_RR = 1,       // ||r||^2
     S_BB = 2,       // ||b||^2 (b mean-removed)
-    S_RZ = 3,       // r . z (current)
+    S_RZ = 3,       // r . z of the iteration whose ALPHA is current
     S_RZOLD = 4,    // r_new . z_old (flexible CG)
     S_ALPHA = 5,
     S_BETA = 6,
@@ -178,7 +178,8 @@ enum Slot {
     S_DS = 15,      // V-cycle scale of the latest direction (outer CG)
     S_APREV = 16,   // the previous outer iteration's ALPHA
     S_PINVBAD = 17, // the coarsest pseudo-inverse met a pivot that is not a positive number
-    S_NSLOTS = 18
+    S_RZNEW = 18,   // r . z of the iteration under way
+    S_NSLOTS = 19
 };
 
 enum FinalizeOp {
@@ -384,6 +385,30 @@ template <>
 struct DirT<double> {
     using type = double;
 };
+// The partial sums of a reduction that the kernel using its scalars adds up by
+// itself (n > 0), in place of a finalising kernel (n == 0: scal is up to date).
+// They lie elsewhere than the kernel's own.
+struct FoldIn {
+    const double *part;
+    int n;
+    size_t pstride;
+    int op;
+    double *scal;      // receives what the sums give
+};
+// Whether a kernel of so many workgroups adds up n doubles itself.  A finalising
+// kernel takes 4 to 5 us and the gap before it 2; each workgroup's own sum 1 us
+// and, together, the time to read them all: at 128^3 the residual update (2048
+// workgroups x 1024 doubles) takes 11.8 us instead of 10.7 and the direction
+// pass 18.7 instead of 17.5, at 256^3 (8192 x 4096) the update 88 instead of 74
+// but the direction pass (2048 x 256) still only 2 more.  FP16 keeps the
+// order of the finalising kernel's sums (fixed_order).
+inline bool folds(Dims d, size_t blocks, size_t n)
+{
+    return !d.fixed_order && blocks * n <= (size_t)1 << 22;
+}
+// workgroups of launch_dir_apply
+template <typename T>
+size_t dir_blocks(Dims d, const double *x);
 // returns the number of partial sums written (at most grid_blocks(red_grid(d)))
 // rho non-null: the link coefficients are formed from the cell densities
 // (the plain operator whose coefficients came from them), not read from bx..bz.
@@ -395,11 +420,11 @@ template <typename T>
 int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const double *bz,
                      const double *rho, const T *z, const typename DirT<T>::type *dold,
                      typename DirT<T>::type *dnew, double *q, double *x, const double *sg,
-                     const double *scal, int mode, double ih2, double *part, size_t pstride,
+                     const double *scal, int mode, double ih2, double *part, size_t pstride, FoldIn in,
                      hipStream_t s);
 template <typename T>
 void launch_pcg_update(Dims d, const double *q, double *r, T *rT, const double *scal, double *part,
-                       hipStream_t s);
+                       FoldIn in, hipStream_t s);
 // x += scal[S_ALPHA] * dv, after x += scal[S_APREV] * dv_prev when dv_prev
 // is given (the two directions still pending after the last iteration)
 template <typename D>

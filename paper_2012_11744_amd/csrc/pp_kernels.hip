@@ -1283,6 +1283,122 @@ __global__ __launch_bounds__(BLOCK) void k_sum(Dims d, const double *__restrict_
     block_partials<1>(v, sm, part, 0);
 }
 
+// flexible CG: beta = (r_k . z_k - r_k . z_{k-1}) / (r_{k-1} . z_{k-1});
+// the stored direction is in units of the V-cycle scale, so its recurrence
+// coefficient is beta s_{k-1} / s_k.  OP_RZ_T: the partials are of r / s_k, the
+// right-hand side the V-cycle was given
+template <typename S>
+__device__ __forceinline__ double new_rz(int op, double s0, const S &scal)
+{
+    return (op == OP_RZ_T ? scal[S_USED] * scal[S_USED] : scal[S_USED]) * s0;
+}
+
+template <typename S>
+__device__ __forceinline__ double next_beta(double rz, const S &scal)
+{
+    return (rz - scal[S_RZOLD]) / scal[S_RZ] * (scal[S_DS] / scal[S_USED]);
+}
+
+// s0 = D . A D with the true direction s_k D: alpha = rz / (s_k^2 s0); the slot
+// holds alpha s_k, the coefficient of D and of q = A D.
+// s1 = D_old . A D: since alpha_k (D_k . A D_k) = r_k . z_k and
+// D_k - z_k = beta_k D_{k-1}, the next residual against this z is
+// r_{k+1} . z_k = alpha_k beta_k (D_{k-1} . A D_k), in stored units
+// alpha s_k * gamma * s_k s1 / s_k (zero on the first iteration, whose gamma is
+// 0 and whose direction pass sums no s1)
+template <typename S>
+__device__ __forceinline__ double next_alpha(double s0, const S &scal)
+{
+    return scal[S_RZNEW] / (scal[S_USED] * s0);
+}
+
+template <typename S, typename Set>
+__device__ __forceinline__ void set_alpha(double alpha, double s0, double s1, const S &scal, Set set)
+{
+    set(S_DQ, s0);
+    set(S_APREV, scal[S_ALPHA]);
+    set(S_ALPHA, alpha);
+    set(S_DS, scal[S_USED]);
+    set(S_RZOLD, alpha * scal[S_BETA] * scal[S_USED] * s1);
+    set(S_RZ, scal[S_RZNEW]);
+}
+
+// The sums of a FoldIn, by every workgroup for itself and in the same order, so
+// with the same bits.
+template <int NQ>
+__device__ __forceinline__ void fold_sums(const FoldIn &in, double (*sm)[BLOCK / 64],
+                                          double (&v)[NQ])
+{
+    const int t = threadIdx.x + BX * threadIdx.y;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        v[q] = 0.0;
+#pragma unroll 2
+    for (int i = t; i < in.n; i += BLOCK)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            v[q] += in.part[q * in.pstride + i];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+            v[q] += __shfl_xor(v[q], o, 64);
+        if ((t & 63) == 0)
+            sm[q][t >> 6] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        v[q] = sm[q][0];
+#pragma unroll
+        for (int w = 1; w < BLOCK / 64; ++w)
+            v[q] += sm[q][w];
+    }
+}
+
+__device__ __forceinline__ bool first_thread()
+{
+    return (threadIdx.x | threadIdx.y | blockIdx.x | blockIdx.y | blockIdx.z) == 0;
+}
+
+// the direction's coefficient: S_BETA, or from the folded sums of r . z.  No
+// workgroup reads the slots that the first one writes.
+// The value is moved to scalar registers, where one loaded from S_BETA would be:
+// the direction pass is short of vector ones.
+__device__ __forceinline__ double uniform(double v)
+{
+    union {
+        double d;
+        int i[2];
+    } u{v};
+    u.i[0] = __builtin_amdgcn_readfirstlane(u.i[0]);
+    u.i[1] = __builtin_amdgcn_readfirstlane(u.i[1]);
+    return u.d;
+}
+
+template <bool FIRST>
+__device__ __forceinline__ double direction_beta(const FoldIn &in, double (*sm)[BLOCK / 64],
+                                                 const double *__restrict__ scal)
+{
+    if (in.n == 0)
+        return FIRST ? 0.0 : scal[S_BETA];
+    double v[1];
+    fold_sums<1>(in, sm, v);
+    const double rz = new_rz(in.op, v[0], scal);
+    const double beta = FIRST ? 0.0 : next_beta(rz, scal);
+    if (first_thread()) {
+        in.scal[S_BETA] = beta;
+        in.scal[S_RZNEW] = rz;
+    }
+    return uniform(beta);
+}
+
+// the scalar array held one value a lane
+struct LaneScal {
+    double v;
+    __device__ __forceinline__ double operator[](int q) const { return __shfl(v, q, 64); }
+};
+
 // Fixed-order sum of the partials (each thread a strided run, then the
 // wave's lanes by butterfly shuffles, then the waves' sums in order), and the
 // scalar update of `op`.  One barrier: the kernel is launched once or more
@@ -1301,6 +1417,11 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restri
     __shared__ double sm[2][FIN_THREADS / 64];
     const bool two = op == OP_INIT || op == OP_ALPHA;
     const int t = threadIdx.x;
+    // the scalars, one a lane of the first wave: loaded beside the partials,
+    // updated in registers, and stored (also to the host) by one instruction
+    // (one thread in turn: 6.0 us with a host copy, now 4.4).  A plain sum may
+    // go to a single double.
+    LaneScal sc{t < S_NSLOTS && (op != OP_STORE || host) ? scal[t] : 0.0};
     // four loads in flight per accumulation step (the sum order stays fixed)
     double a0 = 0.0, a1 = 0.0;
     int i = t;
@@ -1327,7 +1448,7 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restri
         sm[1][t >> 6] = a1;
     }
     __syncthreads();
-    if (t != 0)
+    if (t >= 64)
         return;
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
@@ -1335,69 +1456,57 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double *__restri
         s0 += sm[0][w];
         s1 += sm[1][w];
     }
-    double rms;
+    bool mine = false;                   // the lane's slot changes: others may be written
+                                         // by another stream meanwhile
+    const auto set = [&](int q, double v) {
+        if (t == q) {
+            sc.v = v;
+            mine = true;
+        }
+    };
+    const auto scale = [&](double d) { return d > 0.0 && d < INFINITY ? d : 1.0; };
     switch (op) {
     case OP_STORE:
-        scal[slot] = s0;
+        set(slot, s0);
         break;
     case OP_MEAN:
-        scal[slot] = s0 / ncells;
+        set(slot, s0 / ncells);
         break;
-    case OP_INIT:
-        scal[S_RR] = s0;
-        scal[S_BB] = s1;
-        rms = sqrt(s0 / ncells);
-        if (!(rms > 0.0) || !(rms < INFINITY))
-            rms = 1.0;
-        scal[S_USED] = rms;
-        scal[S_NEXT] = rms;
+    case OP_INIT: {
+        const double rms = scale(sqrt(s0 / ncells));
+        set(S_RR, s0);
+        set(S_BB, s1);
+        set(S_USED, rms);
+        set(S_NEXT, rms);
         break;
+    }
     case OP_RZ:
     case OP_RZ_T: {
-        // flexible CG: beta = (r_k . z_k - r_k . z_{k-1}) / (r_{k-1} . z_{k-1});
-        // the stored direction is in units of the V-cycle scale, so its
-        // recurrence coefficient is beta s_{k-1} / s_k.  OP_RZ_T: the partials
-        // are of r / s_k, the right-hand side the V-cycle was given
-        const double rz = (op == OP_RZ_T ? scal[S_USED] * scal[S_USED] : scal[S_USED]) * s0;
-        scal[S_BETA] =
-            first ? 0.0 : (rz - scal[S_RZOLD]) / scal[S_RZ] * (scal[S_DS] / scal[S_USED]);
-        scal[S_RZ] = rz;
+        const double rz = new_rz(op, s0, sc);
+        set(S_BETA, first ? 0.0 : next_beta(rz, sc));
+        set(S_RZNEW, rz);
         break;
     }
     case OP_ALPHA:
-        // s0 = D . A D with the true direction s_k D: alpha = rz / (s_k^2 s0);
-        // the slot holds alpha s_k, the coefficient of D and of q = A D.
-        // s1 = D_old . A D: since alpha_k (D_k . A D_k) = r_k . z_k and
-        // D_k - z_k = beta_k D_{k-1}, the next residual against this z is
-        // r_{k+1} . z_k = alpha_k beta_k (D_{k-1} . A D_k), in stored units
-        // alpha s_k * gamma * s_k s1 / s_k (zero on the first iteration, whose
-        // gamma is 0 and whose direction pass sums no s1)
-        scal[S_DQ] = s0;
-        scal[S_APREV] = scal[S_ALPHA];
-        scal[S_ALPHA] = scal[S_RZ] / (scal[S_USED] * s0);
-        scal[S_DS] = scal[S_USED];
-        scal[S_RZOLD] = scal[S_ALPHA] * scal[S_BETA] * scal[S_USED] * s1;
+        set_alpha(next_alpha(s0, sc), s0, s1, sc, set);
         break;
     case OP_UPDATE:
-        scal[S_RR] = s0;
-        scal[S_USED] = scal[S_NEXT];
-        rms = sqrt(s0 / ncells);
-        scal[S_NEXT] = (rms > 0.0 && rms < INFINITY) ? rms : 1.0;
-        break;
     case OP_DC:
-        scal[S_RR] = s0;
-        scal[S_USED] = scal[S_NEXT];
-        rms = sqrt(s0 / ncells);
-        scal[S_NEXT] = (rms > 0.0 && rms < INFINITY) ? rms : 1.0;
+        set(S_RR, s0);
+        set(S_USED, sc[S_NEXT]);
+        set(S_NEXT, scale(sqrt(s0 / ncells)));
         break;
     default:
         break;
     }
+    if (mine)
+        scal[t] = sc.v;
     if (host) {
-        for (int q = 0; q < S_NSLOTS; ++q)
-            host[q] = scal[q];
+        if (t < S_NSLOTS)
+            host[t] = sc.v;
         __threadfence_system();   // the values before the ticket
-        *(volatile double *)(host + S_NSLOTS) = ticket;
+        if (t == 0)
+            *(volatile double *)(host + S_NSLOTS) = ticket;
         __threadfence_system();   // visible to the host before the kernel completes
     }
 }
@@ -1744,15 +1853,15 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply(Dims d, Bc bc, const double
                                                      double *__restrict__ x,
                                                      const double *__restrict__ sg,
                                                      const double *__restrict__ scal, double ih2,
-                                                     double *part, size_t pstride)
+                                                     double *part, size_t pstride, FoldIn in)
 {
-    __shared__ double sm[2][BLOCK / 64];
+    __shared__ double sm[2][BLOCK / 64], fsm[1][BLOCK / 64];
     const int i = blockIdx.x * BX + threadIdx.x;
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[2] = {0.0, 0.0};
     constexpr bool FIRST = MODE == DIR_FIRST;
+    const double gamma = direction_beta<FIRST>(in, fsm, scal);
     if (i < d.nx && j < d.ny) {
-        const double gamma = FIRST ? 0.0 : scal[S_BETA];
         const double aold = FIRST ? 0.0 : scal[S_ALPHA];
         const double aprev = MODE == DIR_TWO ? scal[S_APREV] : 0.0;
         auto dv = [&](size_t c) -> double {
@@ -1848,20 +1957,20 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
                                                       double *__restrict__ x,
                                                       const double *__restrict__ sg,
                                                       const double *__restrict__ scal, double ih2,
-                                                      double *part, size_t pstride)
+                                                      double *part, size_t pstride, FoldIn in)
 {
     using T2 = typename Vec2<T>::type;
     using D2 = typename Vec2<D>::type;
     using F2 = double __attribute__((ext_vector_type(2)));
-    __shared__ double sm[2][BLOCK / 64];
+    __shared__ double sm[2][BLOCK / 64], fsm[1][BLOCK / 64];
     unsigned gbx, gby, gbz;
     xcd_groups(gbx, gby, gbz);
     const int x0 = 2 * (int)(gbx * BX + threadIdx.x);
     const int j0 = 2 * (int)(gby * BY + threadIdx.y), j1 = j0 + 1;
     double v[2] = {0.0, 0.0};
     constexpr bool FIRST = MODE == DIR_FIRST;
+    const double gamma = direction_beta<FIRST>(in, fsm, scal);
     if (x0 < d.nx && j0 < d.ny) {
-        const double gamma = FIRST ? 0.0 : scal[S_BETA];
         const double aold = FIRST ? 0.0 : scal[S_ALPHA];
         const double aprev = MODE == DIR_TWO ? scal[S_APREV] : 0.0;
         const size_t sy = (size_t)d.nx, sz = (size_t)d.nx * d.ny;
@@ -2056,14 +2165,22 @@ template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_pcg_update(Dims d, const double *__restrict__ q,
                                                       double *__restrict__ r, T *__restrict__ rT,
                                                       const double *__restrict__ scal,
-                                                      double *part)
+                                                      double *part, FoldIn in)
 {
-    __shared__ double sm[1][BLOCK / 64];
+    __shared__ double sm[1][BLOCK / 64], fsm[2][BLOCK / 64];
     const int i = blockIdx.x * BX + threadIdx.x;
     const int j = blockIdx.y * BY + threadIdx.y;
-    double v[1] = {0.0};
+    double v[1] = {0.0}, alpha;
+    if (in.n) {
+        double f[2];
+        fold_sums<2>(in, fsm, f);
+        alpha = uniform(next_alpha(f[0], scal));
+        if (first_thread())
+            set_alpha(alpha, f[0], f[1], scal, [&](int q, double v) { in.scal[q] = v; });
+    } else {
+        alpha = scal[S_ALPHA];
+    }
     if (i < d.nx && j < d.ny) {
-        const double alpha = scal[S_ALPHA];
         const double inv = 1.0 / scal[S_NEXT];
         const int kz = block_planes(d.nz);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
@@ -2442,20 +2559,34 @@ void launch_dot_rz(Dims d, const double *r, const T *z, double *part, hipStream_
 }
 
 
+// 2 x 2 cells per thread where the grid and the iterate allow pairs
+bool dir_quad(Dims d, const double *x) { return d.nx % 2 == 0 && d.ny % 2 == 0 && ((uintptr_t)x & 15) == 0; }
+
+template <typename T>
+dim3 dir_grid(Dims d, const double *x)
+{
+    return dir_quad(d, x) ? quad_grid(d, sizeof(typename DirT<T>::type) == 8) : red_grid(d);
+}
+
+template <typename T>
+size_t dir_blocks(Dims d, const double *x)
+{
+    return grid_blocks(dir_grid<T>(d, x));
+}
+
 template <typename T>
 int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const double *bz,
                      const double *rho, const T *z, const typename DirT<T>::type *dold,
                      typename DirT<T>::type *dnew, double *q, double *x, const double *sg,
-                     const double *scal, int mode, double ih2, double *part, size_t pstride,
+                     const double *scal, int mode, double ih2, double *part, size_t pstride, FoldIn in,
                      hipStream_t s)
 {
     using D = typename DirT<T>::type;
-    // 2 x 2 cells per thread where the grid and the iterate allow pairs
-    const bool quad = d.nx % 2 == 0 && d.ny % 2 == 0 && ((uintptr_t)x & 15) == 0;
-    const dim3 g = quad ? quad_grid(d, sizeof(D) == 8) : red_grid(d);
+    const bool quad = dir_quad(d, x);
+    const dim3 g = dir_grid<T>(d, x);
     auto go = [&](auto kern) {
         PP_LAUNCH(kern, g, kBlock, 0, s, d, bc, bx, by, bz, rho, z, dold, dnew, q, x, sg,
-                  scal, ih2, part, pstride);
+                  scal, ih2, part, pstride, in);
     };
     auto by_mode = [&](auto r) {
         constexpr bool RH = decltype(r)::value;
@@ -2484,9 +2615,9 @@ int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const do
 
 template <typename T>
 void launch_pcg_update(Dims d, const double *q, double *r, T *rT, const double *scal, double *part,
-                       hipStream_t s)
+                       FoldIn in, hipStream_t s)
 {
-    PP_LAUNCH((k_pcg_update<T>), red_grid(d), kBlock, 0, s, d, q, r, rT, scal, part);
+    PP_LAUNCH((k_pcg_update<T>), red_grid(d), kBlock, 0, s, d, q, r, rT, scal, part, in);
 }
 
 template <typename D>
@@ -2535,14 +2666,15 @@ void launch_sub_mean(size_t n, double *x, const double *scal, int slot, const un
     template void launch_scale_T<T>(size_t, const double *, T *, const double *, hipStream_t);  \
     template void launch_axpy_T<T>(size_t, const T *, double *, const double *, hipStream_t);   \
     template void launch_dot_rz<T>(Dims, const double *, const T *, double *, hipStream_t);     \
+    template size_t dir_blocks<T>(Dims, const double *);                                        \
     template int launch_dir_apply<T>(Dims, Bc, const double *, const double *, const double *,  \
                                       const double *, const T *,                                \
                                       const typename DirT<T>::type *,                           \
                                       typename DirT<T>::type *, double *, double *,             \
                                       const double *, const double *, int, double, double *,    \
-                                      size_t, hipStream_t);                                     \
+                                      size_t, FoldIn, hipStream_t);                             \
     template void launch_pcg_update<T>(Dims, const double *, double *, T *, const double *,     \
-                                       double *, hipStream_t);
+                                       double *, FoldIn, hipStream_t);
 
 PP_INSTANTIATE(double)
 PP_INSTANTIATE(float)

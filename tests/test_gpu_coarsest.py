@@ -224,3 +224,32 @@ def test_two_sweep_pass_beyond_2_gib(S, zero):
     assert big[0].numel() * 4 > 2 ** 31
     diff = max((o - outs[0]).abs().max().item() for o in outs[1].view(rep, per, ny, nx))
     assert diff <= 4 * 4 * 2.0 ** -24 * outs[0].abs().max().item()
+
+
+# (nx, ny, nz): one workgroup, odd sizes (a cell per thread), 2 x 2 cells, more
+# partial sums than threads, and a level whose residual update leaves its sums
+# to a kernel of their own
+SOLVES = [(4, 4, 4), (9, 11, 9), (24, 20, 28), (96, 80, 64), (256, 192, 128)]
+
+
+@pytest.mark.parametrize("n", SOLVES)
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_solve_scalars(S, n, precision):
+    """The step lengths and direction coefficients that the outer iteration's
+    kernels form for themselves: the true residual meets the tolerance that the
+    recurrence reports (its drift is a few eps per iteration), and a repeat
+    gives the same bits."""
+    shape = (n[2], n[1], n[0])
+    g = torch.Generator().manual_seed(9)
+    beta = [(10.0 ** -torch.rand(shape, generator=g, dtype=torch.float64)).cuda()
+            for _ in range(3)]
+    beta[2][0] = 0.0
+    b = torch.rand(shape, generator=g, dtype=torch.float64).cuda()
+    b -= b.mean()
+    with S.Solver(beta, 1.0 / n[0], (0, 0, 1), precision=precision, coarsest=1024) as sol:
+        p = sol.solve(b, tol=1e-9).clone()
+        again = sol.solve(b, tol=1e-9)
+        rel = float((b - sol.apply(p)).norm() / b.norm())
+    print(n, precision, "rel %.3e" % rel, flush=True)
+    assert torch.equal(p, again)
+    assert rel <= 1e-9 * (1 + 1e-3) + 1e-12
