@@ -129,6 +129,18 @@ inline dim3 quad_grid(Dims d, bool wide)
     return dim3(gx, gy, (d.nz + kz - 1) / kz);
 }
 
+// Grids whose arrays outgrow the caches between two passes: there the direction
+// pass, the residual update and the projection mark what they stream (q, the
+// stored direction, the iterate, r, the velocities) as non-temporal, so that it
+// leaves the halo rows and the arrays of the next pass in them.  256^3 FP32 step
+// with / without: direction pass 120 / 125 us (two directions 164 / 171), the
+// smoother's first pass behind the update 95 / 103, projection 193 / 213, step 2.8%,
+// FP64 solve 3.9%; steps at 160^3 1.3% and 2.7% faster, at 128^3 1 to 2% slower
+// (all of it fits).  The smoother, the prolongation's weights and the loads
+// gained nothing.
+constexpr size_t STREAM_CELLS = (size_t)3 << 20;
+inline bool streams(Dims d) { return cells(d) > STREAM_CELLS; }
+
 // grid of the one-pass coefficient loads: a thread per coarse column
 inline dim3 load_grid(Dims fd)
 {

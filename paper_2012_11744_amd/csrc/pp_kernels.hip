@@ -128,6 +128,26 @@ __device__ __forceinline__ void block_partials(double (&v)[NQ], double (*sm)[BLO
     }
 }
 
+// Accesses to values that are not needed again before the caches have turned
+// over, with the non-temporal hint where NT.
+template <bool NT, typename V>
+__device__ __forceinline__ V ld_once(const V *p)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
+template <bool NT, typename V>
+__device__ __forceinline__ void st_once(V *p, V v)
+{
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // Workgroups are dispatched to the 8 XCDs in turn and each XCD has its own L2.
 // The stencil kernels with 2 x 2 cells per thread take their blocks in groups
 // of all x-blocks of two block rows, one group per XCD in turn: the halo lines
@@ -1168,7 +1188,7 @@ __global__ __launch_bounds__(BLOCK) void k_apply(Dims d, Bc bc, const double *__
 // links (beta = 0: the link flags multiply the velocity) (eq. fotm).
 // u may alias us: each thread reads and writes only its own entries.  RHO:
 // beta formed from the cell densities (as in k_dir_apply).
-template <bool RHO>
+template <bool RHO, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_project(Dims d, Bc bc, const double *__restrict__ bx,
                                                    const double *__restrict__ by,
                                                    const double *__restrict__ bz,
@@ -1195,12 +1215,12 @@ __global__ __launch_bounds__(BLOCK) void k_project(Dims d, Bc bc, const double *
         fy = by[n.c];
         fz = bz[n.c];
     }
-    const double vx = (n.wxl || fx == 0.0) ? 0.0 : usx[n.c] - dt_h * fx * (pc - p[n.xm]);
-    const double vy = (n.wyl || fy == 0.0) ? 0.0 : usy[n.c] - dt_h * fy * (pc - p[n.ym]);
-    const double vz = (n.wzl || fz == 0.0) ? 0.0 : usz[n.c] - dt_h * fz * (pc - p[n.zm]);
-    ux[n.c] = vx;
-    uy[n.c] = vy;
-    uz[n.c] = vz;
+    const double vx = (n.wxl || fx == 0.0) ? 0.0 : ld_once<NT>(usx + n.c) - dt_h * fx * (pc - p[n.xm]);
+    const double vy = (n.wyl || fy == 0.0) ? 0.0 : ld_once<NT>(usy + n.c) - dt_h * fy * (pc - p[n.ym]);
+    const double vz = (n.wzl || fz == 0.0) ? 0.0 : ld_once<NT>(usz + n.c) - dt_h * fz * (pc - p[n.zm]);
+    st_once<NT>(ux + n.c, vx);
+    st_once<NT>(uy + n.c, vy);
+    st_once<NT>(uz + n.c, vz);
 }
 
 // g_beta_m = G_m lambda * G_m p on non-wall faces, 0 on walls
@@ -1945,7 +1965,7 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply(Dims d, Bc bc, const double
 // many of them here.  The faces between the block's cells are formed once.
 // Same arithmetic per cell as k_dir_apply (same order of terms), and the same
 // iterate updates (MODE).
-template <typename T, typename D, int MODE, bool RHO>
+template <typename T, typename D, int MODE, bool RHO, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const double *__restrict__ bx,
                                                       const double *__restrict__ by,
                                                       const double *__restrict__ bz,
@@ -2122,22 +2142,24 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
             }
             if (MODE == DIR_TWO) {
                 // D_{k-2} is what dnew holds until the stores below
-                const D2 ea = *reinterpret_cast<const D2 *>(dnew + pl + o0);
-                const D2 eb = *reinterpret_cast<const D2 *>(dnew + pl + o1);
+                const D2 ea = ld_once<NT>(reinterpret_cast<const D2 *>(dnew + pl + o0));
+                const D2 eb = ld_once<NT>(reinterpret_cast<const D2 *>(dnew + pl + o1));
                 F2 *xa = reinterpret_cast<F2 *>(x + pl + o0);
                 F2 *xb = reinterpret_cast<F2 *>(x + pl + o1);
-                F2 va = *xa, vb = *xb;
+                F2 va = ld_once<NT>(xa), vb = ld_once<NT>(xb);
                 va.x = (va.x + aprev * static_cast<double>(ea.x)) + aold * Oc[0];
                 va.y = (va.y + aprev * static_cast<double>(ea.y)) + aold * Oc[1];
                 vb.x = (vb.x + aprev * static_cast<double>(eb.x)) + aold * Oc[2];
                 vb.y = (vb.y + aprev * static_cast<double>(eb.y)) + aold * Oc[3];
-                *xa = va;
-                *xb = vb;
+                st_once<NT>(xa, va);
+                st_once<NT>(xb, vb);
             }
-            *reinterpret_cast<D2 *>(dnew + pl + o0) = D2{static_cast<D>(Dc[0]), static_cast<D>(Dc[1])};
-            *reinterpret_cast<D2 *>(dnew + pl + o1) = D2{static_cast<D>(Dc[2]), static_cast<D>(Dc[3])};
-            *reinterpret_cast<F2 *>(q + pl + o0) = F2{qq[0], qq[1]};
-            *reinterpret_cast<F2 *>(q + pl + o1) = F2{qq[2], qq[3]};
+            st_once<NT>(reinterpret_cast<D2 *>(dnew + pl + o0),
+                        D2{static_cast<D>(Dc[0]), static_cast<D>(Dc[1])});
+            st_once<NT>(reinterpret_cast<D2 *>(dnew + pl + o1),
+                        D2{static_cast<D>(Dc[2]), static_cast<D>(Dc[3])});
+            st_once<NT>(reinterpret_cast<F2 *>(q + pl + o0), F2{qq[0], qq[1]});
+            st_once<NT>(reinterpret_cast<F2 *>(q + pl + o1), F2{qq[2], qq[3]});
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 v[0] += Dc[c] * qq[c];
@@ -2161,7 +2183,7 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
 // r -= a q (a = scal[S_ALPHA]); rT = r / scal[S_NEXT]; partial ||r||^2.
 // The iterate takes the matching x += a D in a later direction pass (two
 // directions at a time), or in k_axpy_dir after the last iteration.
-template <typename T>
+template <typename T, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_pcg_update(Dims d, const double *__restrict__ q,
                                                       double *__restrict__ r, T *__restrict__ rT,
                                                       const double *__restrict__ scal,
@@ -2186,8 +2208,8 @@ __global__ __launch_bounds__(BLOCK) void k_pcg_update(Dims d, const double *__re
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
-            const double rn = r[c] - alpha * q[c];
-            r[c] = rn;
+            const double rn = ld_once<NT>(r + c) - alpha * ld_once<NT>(q + c);
+            st_once<NT>(r + c, rn);
             rT[c] = static_cast<T>(rn * inv);
             v[0] += rn * rn;
         }
@@ -2455,12 +2477,14 @@ void launch_project(Dims d, Bc bc, const double *bx, const double *by, const dou
                     const double *p, double dt_over_h, double *ux, double *uy, double *uz,
                     hipStream_t s)
 {
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, cell_grid(d), kBlock, 0, s, d, bc, bx, by, bz, rho, usx, usy, usz,
+                           p, dt_over_h, ux, uy, uz);
+    };
     if (rho)
-        hipLaunchKernelGGL(k_project<true>, cell_grid(d), kBlock, 0, s, d, bc, bx, by, bz, rho, usx,
-                           usy, usz, p, dt_over_h, ux, uy, uz);
+        streams(d) ? go(k_project<true, true>) : go(k_project<true, false>);
     else
-        hipLaunchKernelGGL(k_project<false>, cell_grid(d), kBlock, 0, s, d, bc, bx, by, bz, rho,
-                           usx, usy, usz, p, dt_over_h, ux, uy, uz);
+        streams(d) ? go(k_project<false, true>) : go(k_project<false, false>);
 }
 
 void launch_adjoint_faces(Dims d, Bc bc, const double *lam, const double *p, double ih2,
@@ -2588,15 +2612,15 @@ int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const do
         PP_LAUNCH(kern, g, kBlock, 0, s, d, bc, bx, by, bz, rho, z, dold, dnew, q, x, sg,
                   scal, ih2, part, pstride, in);
     };
-    auto by_mode = [&](auto r) {
-        constexpr bool RH = decltype(r)::value;
+    auto by_mode = [&](auto r, auto nt) {
+        constexpr bool RH = decltype(r)::value, NT = decltype(nt)::value;
         if (quad) {
             if (mode == DIR_FIRST)
-                go(k_dir_apply2<T, D, DIR_FIRST, RH>);
+                go(k_dir_apply2<T, D, DIR_FIRST, RH, NT>);
             else if (mode == DIR_HOLD)
-                go(k_dir_apply2<T, D, DIR_HOLD, RH>);
+                go(k_dir_apply2<T, D, DIR_HOLD, RH, NT>);
             else
-                go(k_dir_apply2<T, D, DIR_TWO, RH>);
+                go(k_dir_apply2<T, D, DIR_TWO, RH, NT>);
         } else {
             if (mode == DIR_FIRST)
                 go(k_dir_apply<T, D, DIR_FIRST, RH>);
@@ -2606,10 +2630,16 @@ int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const do
                 go(k_dir_apply<T, D, DIR_TWO, RH>);
         }
     };
+    auto by_size = [&](auto r) {
+        if (quad && streams(d))
+            by_mode(r, std::true_type{});
+        else
+            by_mode(r, std::false_type{});
+    };
     if (rho)
-        by_mode(std::true_type{});
+        by_size(std::true_type{});
     else
-        by_mode(std::false_type{});
+        by_size(std::false_type{});
     return (int)grid_blocks(g);
 }
 
@@ -2617,7 +2647,10 @@ template <typename T>
 void launch_pcg_update(Dims d, const double *q, double *r, T *rT, const double *scal, double *part,
                        FoldIn in, hipStream_t s)
 {
-    PP_LAUNCH((k_pcg_update<T>), red_grid(d), kBlock, 0, s, d, q, r, rT, scal, part, in);
+    auto go = [&](auto kern) {
+        PP_LAUNCH(kern, red_grid(d), kBlock, 0, s, d, q, r, rT, scal, part, in);
+    };
+    streams(d) ? go(k_pcg_update<T, true>) : go(k_pcg_update<T, false>);
 }
 
 template <typename D>

@@ -253,3 +253,23 @@ def test_solve_scalars(S, n, precision):
     print(n, precision, "rel %.3e" % rel, flush=True)
     assert torch.equal(p, again)
     assert rel <= 1e-9 * (1 + 1e-3) + 1e-12
+
+
+@pytest.mark.parametrize("n", [(192, 128, 128), (256, 160, 80)])
+def test_projection_either_side_of_the_cache_size(S, n):
+    """u = u* - dt beta grad p below and above the size from which the velocities
+    are streamed: three roundings of values up to the larger term."""
+    shape = (n[2], n[1], n[0])
+    g = torch.Generator().manual_seed(4)
+    beta, us = ([torch.rand(shape, generator=g, dtype=torch.float64).cuda() + 0.5
+                 for _ in range(3)] for _ in range(2))
+    beta[1][:, 0] = 0.0
+    p = torch.rand(shape, generator=g, dtype=torch.float64).cuda()
+    h, dt = 0.25, 0.125
+    with S.Solver(beta, h, (0, 1, 0), precision="fp32") as sol:
+        u = sol.project(us, p, dt)
+    for m in range(3):
+        want = us[m] - dt / h * beta[m] * (p - torch.roll(p, 1, 2 - m))
+        if m == 1:
+            want[:, 0] = 0.0
+        assert float((u[m] - want).abs().max()) <= 4 * 2.0 ** -52 * 2.5
