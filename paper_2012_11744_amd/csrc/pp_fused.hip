@@ -575,6 +575,14 @@ struct GsLag {
 __device__ __forceinline__ float om_over(float om, float d) { return om * __builtin_amdgcn_rcpf(d); }
 __device__ __forceinline__ double om_over(double om, double d) { return om / d; }
 
+// a b, kept a product of its own (no contraction with the sum that takes it)
+template <typename C>
+__device__ __forceinline__ C rounded_product(C a, C b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 // om: the over-relaxation of eq. beta_pressure, folded into the reciprocal
 // diagonal that the lag registers carry (inv = om / diag), so every phase
 // forms e <- (1 - om) e + inv (sum - h^2 r); the old value of phases A and B
@@ -895,9 +903,9 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
         if (DOT)
             rc = a2.r;
         a2 = a1;
-        a1 = GsLag<C>{xi, xo, yl, yh, zl, zh, inva, EXACT ? h2 * ra : ra};
+        a1 = GsLag<C>{xi, xo, yl, yh, zl, zh, inva, EXACT ? rounded_product(h2, ra) : ra};
         b2 = b1;
-        b1 = GsLag<C>{sxi, sxo, syl, syh, bzl, bzh, invb, EXACT ? h2 * rb : rb};
+        b1 = GsLag<C>{sxi, sxo, syl, syh, bzl, bzh, invb, EXACT ? rounded_product(h2, rb) : rb};
         sxi = xi;
         sxo = nxo;
         syl = nyl;
