@@ -1106,15 +1106,14 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
             nrz = np;
             op = OP_RZ;
         }
+        // the iterate takes the pending directions two at a time: the passes of
+        // odd iterations hold theirs, those of even ones apply the last two
+        const int mode = first ? DIR_FIRST : ((launched & 1) ? DIR_HOLD : DIR_TWO);
         FoldIn rz{c->part, nrz, c->pstride, op, c->scal};
         settle(rz, dir_blocks<T>(c->d, x), nrz);
         int npd;
         {
             KT t(c, PP_KT_OUTER_APPLY, true);
-            // the iterate takes the pending directions two at a time: the
-            // passes of odd iterations hold theirs, those of even ones apply
-            // the last two
-            const int mode = first ? DIR_FIRST : ((launched & 1) ? DIR_HOLD : DIR_TWO);
             if (!op_rho(c))
                 PP_TRY(ensure_b64(c));
             npd = launch_dir_apply<T>(c->d, c->bc, c->chain[0][0], c->chain[0][1], c->chain[0][2],

@@ -133,11 +133,12 @@ inline dim3 quad_grid(Dims d, bool wide)
 // pass, the residual update and the projection mark what they stream (q, the
 // stored direction, the iterate, r, the velocities) as non-temporal, so that it
 // leaves the halo rows and the arrays of the next pass in them.  256^3 FP32 step
-// with / without: direction pass 120 / 125 us (two directions 164 / 171), the
+// with / without: k_dir_apply2 120 / 125 us (two directions 164 / 171), the
 // smoother's first pass behind the update 95 / 103, projection 193 / 213, step 2.8%,
 // FP64 solve 3.9%; steps at 160^3 1.3% and 2.7% faster, at 128^3 1 to 2% slower
-// (all of it fits).  The smoother, the prolongation's weights and the loads
-// gained nothing.
+// (all of it fits).  The smoother's passes lost (112 us, 115 to 122 with the hint),
+// the prolongation's weights and the loads gained nothing.  The direction pass is
+// k_dir_rows from here on.
 constexpr size_t STREAM_CELLS = (size_t)3 << 20;
 inline bool streams(Dims d) { return cells(d) > STREAM_CELLS; }
 
@@ -428,6 +429,9 @@ size_t dir_blocks(Dims d, const double *x);
 // DIR_HOLD none (its direction waits a pass), DIR_TWO x += APREV * (dnew as
 // it was, D_{k-2}) + ALPHA * D_old, the two pending directions.
 enum DirMode { DIR_FIRST = 0, DIR_HOLD = 1, DIR_TWO = 2 };
+// Workgroups of k_dir_rows that a CU holds: what its registers are kept to.  With
+// three the two-direction and FP64 forms spill (154 -> 245 us, 172 -> 237).
+constexpr int dir_per_cu(size_t stored, int mode) { return mode == DIR_TWO || stored == 8 ? 2 : 3; }
 template <typename T>
 int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const double *bz,
                      const double *rho, const T *z, const typename DirT<T>::type *dold,

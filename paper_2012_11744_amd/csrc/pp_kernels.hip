@@ -1965,7 +1965,7 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply(Dims d, Bc bc, const double
 // many of them here.  The faces between the block's cells are formed once.
 // Same arithmetic per cell as k_dir_apply (same order of terms), and the same
 // iterate updates (MODE).
-template <typename T, typename D, int MODE, bool RHO, bool NT>
+template <typename T, typename D, int MODE, bool RHO>
 __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const double *__restrict__ bx,
                                                       const double *__restrict__ by,
                                                       const double *__restrict__ bz,
@@ -2142,24 +2142,22 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
             }
             if (MODE == DIR_TWO) {
                 // D_{k-2} is what dnew holds until the stores below
-                const D2 ea = ld_once<NT>(reinterpret_cast<const D2 *>(dnew + pl + o0));
-                const D2 eb = ld_once<NT>(reinterpret_cast<const D2 *>(dnew + pl + o1));
+                const D2 ea = *reinterpret_cast<const D2 *>(dnew + pl + o0);
+                const D2 eb = *reinterpret_cast<const D2 *>(dnew + pl + o1);
                 F2 *xa = reinterpret_cast<F2 *>(x + pl + o0);
                 F2 *xb = reinterpret_cast<F2 *>(x + pl + o1);
-                F2 va = ld_once<NT>(xa), vb = ld_once<NT>(xb);
+                F2 va = *xa, vb = *xb;
                 va.x = (va.x + aprev * static_cast<double>(ea.x)) + aold * Oc[0];
                 va.y = (va.y + aprev * static_cast<double>(ea.y)) + aold * Oc[1];
                 vb.x = (vb.x + aprev * static_cast<double>(eb.x)) + aold * Oc[2];
                 vb.y = (vb.y + aprev * static_cast<double>(eb.y)) + aold * Oc[3];
-                st_once<NT>(xa, va);
-                st_once<NT>(xb, vb);
+                *xa = va;
+                *xb = vb;
             }
-            st_once<NT>(reinterpret_cast<D2 *>(dnew + pl + o0),
-                        D2{static_cast<D>(Dc[0]), static_cast<D>(Dc[1])});
-            st_once<NT>(reinterpret_cast<D2 *>(dnew + pl + o1),
-                        D2{static_cast<D>(Dc[2]), static_cast<D>(Dc[3])});
-            st_once<NT>(reinterpret_cast<F2 *>(q + pl + o0), F2{qq[0], qq[1]});
-            st_once<NT>(reinterpret_cast<F2 *>(q + pl + o1), F2{qq[2], qq[3]});
+            *reinterpret_cast<D2 *>(dnew + pl + o0) = D2{static_cast<D>(Dc[0]), static_cast<D>(Dc[1])};
+            *reinterpret_cast<D2 *>(dnew + pl + o1) = D2{static_cast<D>(Dc[2]), static_cast<D>(Dc[3])};
+            *reinterpret_cast<F2 *>(q + pl + o0) = F2{qq[0], qq[1]};
+            *reinterpret_cast<F2 *>(q + pl + o1) = F2{qq[2], qq[3]};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 v[0] += Dc[c] * qq[c];
@@ -2175,6 +2173,347 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
                 if (RHO)
                     Rc[c] = Rp[c];
             }
+        }
+    }
+    block_partials<2>(v, sm, part, pstride);
+}
+
+// v of the lane that CTRL names, old where there is none
+template <int CTRL>
+__device__ __forceinline__ double dpp(double old, double v)
+{
+    union {
+        double d;
+        int i[2];
+    } a{old}, b{v};
+    b.i[0] = __builtin_amdgcn_update_dpp(a.i[0], b.i[0], CTRL, 0xf, 0xf, false);
+    b.i[1] = __builtin_amdgcn_update_dpp(a.i[1], b.i[1], CTRL, 0xf, 0xf, false);
+    return b.d;
+}
+
+// k_dir_apply2 for grids that outgrow the caches.  There its 24 loads a plane and
+// thread, all consumed at once, bounded it: 5.7 us a plane step with three
+// workgroups a CU, whatever the order of the blocks or the length of the chunks.
+// Here a cell's D and coefficients are loaded and formed once in the block: a wave
+// holds two whole rows, so neighbours along x come from the lanes beside (DPP),
+// those along y from LDS (a barrier a plane), and only the first and last lanes
+// and waves load the cells beyond the block; lanes and rows just past the grid's
+// end hold the wrapped cells.  The next plane's loads are issued before this
+// plane's x and y terms.  What it streams carries the non-temporal hint.  Same
+// arithmetic per cell, same sums.  256^3 FP32 103 us (two directions 154, first
+// 88), before 120 (164, 95); FP64 from coefficients 172 (235), before 188 (248).
+// Smaller grids gain nothing (128^3 18.2 / 22.7 us against 18.4 / 22.1) or
+// lose a round of workgroups (160 x 128 x 96 25 / 38 against 24 / 29).
+template <typename T, typename D, int MODE, bool RHO>
+__global__ __launch_bounds__(BLOCK, dir_per_cu(sizeof(D), MODE)) void k_dir_rows(Dims d, Bc bc, const double *__restrict__ bx,
+                                                    const double *__restrict__ by,
+                                                    const double *__restrict__ bz,
+                                                    const double *__restrict__ rho,
+                                                    const T *__restrict__ z,
+                                                    const D *__restrict__ dold,
+                                                    D *__restrict__ dnew,
+                                                    double *__restrict__ q,
+                                                    double *__restrict__ x,
+                                                    const double *__restrict__ sg,
+                                                    const double *__restrict__ scal, double ih2,
+                                                    double *part, size_t pstride, FoldIn in)
+{
+    using T2 = typename Vec2<T>::type;
+    using D2 = typename Vec2<D>::type;
+    using F2 = double __attribute__((ext_vector_type(2)));
+    static_assert(BX == 64, "a wave holds two whole rows of the block");
+    __shared__ double sm[2][BLOCK / 64], fsm[1][BLOCK / 64];
+    // planes k and k + 1: the direction and the densities (RHO) or beta_y, by row
+    // from the one below the block; and the cells beyond its ends in x of the
+    // direction and the densities or beta_x
+    __shared__ F2 SD[2][2 * BY + 2][BX], SF[2][2 * BY + 2][BX];
+    __shared__ double ED[2][2 * BY][2], EF[2][2 * BY][2];
+    unsigned gbx, gby, gbz;
+    xcd_groups(gbx, gby, gbz);
+    const int tx = threadIdx.x, ty = threadIdx.y;
+    const int xu = 2 * ((int)gbx * BX + tx), ju = 2 * ((int)gby * BY + ty);
+    const bool act = xu < d.nx && ju < d.ny;
+    const int x0 = xu < d.nx ? xu : 0, j0 = ju < d.ny ? ju : 0, j1 = j0 + 1;
+    constexpr bool FIRST = MODE == DIR_FIRST;
+    const double gamma = direction_beta<FIRST>(in, fsm, scal);
+    const double aold = FIRST ? 0.0 : scal[S_ALPHA];
+    const double aprev = MODE == DIR_TWO ? scal[S_APREV] : 0.0;
+    const size_t sz = (size_t)d.nx * d.ny;
+    // the cell beyond the block's end in the first and last lanes, the row beyond
+    // it in the first and last waves
+    const bool edge = tx == 0 || tx == BX - 1, beyond = ty == 0 || ty == BY - 1;
+    const int xe = tx == 0 ? (x0 == 0 ? d.nx - 1 : x0 - 1) : (x0 + 2 == d.nx ? 0 : x0 + 2);
+    const int jb = ty == 0 ? (j0 == 0 ? d.ny - 1 : j0 - 1) : (j1 + 1 == d.ny ? 0 : j1 + 1);
+    const bool wxl = bc.x && x0 == 0, wxh = bc.x && x0 + 2 == d.nx;
+    const bool wyl = bc.y && j0 == 0, wyh = bc.y && j1 == d.ny - 1;
+    // in-plane indices; a plane's base is uniform and its bytes fit 32 bits
+    const unsigned nx = d.nx;
+    const unsigned o0 = j0 * nx + x0, o1 = o0 + nx;
+    const unsigned e0 = j0 * nx + xe, e1 = e0 + nx, ob = jb * nx + x0;
+    auto at = [](auto *base, size_t pl, unsigned o) {
+        using E = std::remove_pointer_t<decltype(base)>;
+        using B = std::conditional_t<std::is_const<E>::value, const char, char>;
+        return reinterpret_cast<E *>(reinterpret_cast<B *>(base + pl) + o * (unsigned)sizeof(E));
+    };
+    auto dcast = [&](double t, double o) -> double {
+        return static_cast<double>(static_cast<D>(FIRST ? t : __builtin_fma(gamma, o, t)));
+    };
+    auto ld2d = [&](const double *p, size_t pl, unsigned o) -> F2 {
+        return *reinterpret_cast<const F2 *>(at(p, pl, o));
+    };
+    auto ldT = [&](size_t pl, unsigned o) -> T2 { return *reinterpret_cast<const T2 *>(at(z, pl, o)); };
+    auto ldD = [&](size_t pl, unsigned o) -> D2 {
+        return *reinterpret_cast<const D2 *>(at(dold, pl, o));
+    };
+    // a plane's values as loaded: own rows, edge cells, the row beyond.  f0, f1 are
+    // rho's rows, or beta_z's; fe rho's edge cells, or beta_x's; fb rho's row
+    // beyond, or beta_y's
+    struct Raw {
+        T2 z0, z1, zb;
+        D2 d0, d1, db;
+        F2 f0, f1, fb;
+        T ze[2];
+        D de[2];
+        double fe[2];
+    };
+    auto load = [&](size_t pl, bool halo, Raw &r) {
+        r.z0 = ldT(pl, o0);
+        r.z1 = ldT(pl, o1);
+        if (!FIRST) {
+            r.d0 = ldD(pl, o0);
+            r.d1 = ldD(pl, o1);
+        }
+        r.f0 = ld2d(RHO ? rho : bz, pl, o0);
+        r.f1 = ld2d(RHO ? rho : bz, pl, o1);
+        if (!halo)
+            return;
+        if (beyond) {
+            r.zb = ldT(pl, ob);
+            if (!FIRST)
+                r.db = ldD(pl, ob);
+            r.fb = ld2d(RHO ? rho : by, pl, ob);
+        }
+        if (edge) {
+            r.ze[0] = *at(z, pl, e0);
+            r.ze[1] = *at(z, pl, e1);
+            if (!FIRST) {
+                r.de[0] = *at(dold, pl, e0);
+                r.de[1] = *at(dold, pl, e1);
+            }
+            r.fe[0] = *at(RHO ? rho : bx, pl, e0);
+            r.fe[1] = *at(RHO ? rho : bx, pl, e1);
+        }
+    };
+    // the lane's neighbours along x: own halves b of the lane below (a of the lane
+    // above), the edge value in the first (last) lane
+    auto from_left = [](double v, double ev) { return dpp<0x138>(ev, v); };
+    auto from_right = [](double v, double ev) { return dpp<0x130>(ev, v); };
+    // cells 0: (x0, j0), 1: (x0 + 1, j0), 2: (x0, j1), 3: (x0 + 1, j1)
+    const int kz = block_planes(d.nz);
+    const int k0 = (int)gbz * kz;
+    const int ke = min(d.nz, k0 + kz);
+    const size_t pm = (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz, pc0 = (size_t)k0 * sz;
+    double v[2] = {0.0, 0.0};
+    double Dm[4], Dc[4], ZL[4], Rc[4];
+    D Oc[4];
+    // the direction (and D_old) of a loaded plane
+    auto own = [&](const Raw &r, double (&Dn)[4], D (&On)[4]) {
+        if (!FIRST) {
+            On[0] = r.d0.x;
+            On[1] = r.d0.y;
+            On[2] = r.d1.x;
+            On[3] = r.d1.y;
+        }
+        Dn[0] = dcast(static_cast<double>(r.z0.x), FIRST ? 0.0 : static_cast<double>(On[0]));
+        Dn[1] = dcast(static_cast<double>(r.z0.y), FIRST ? 0.0 : static_cast<double>(On[1]));
+        Dn[2] = dcast(static_cast<double>(r.z1.x), FIRST ? 0.0 : static_cast<double>(On[2]));
+        Dn[3] = dcast(static_cast<double>(r.z1.y), FIRST ? 0.0 : static_cast<double>(On[3]));
+    };
+    const int le = tx == 0 ? 0 : 1, lb = ty == 0 ? 0 : 2 * BY + 1;
+    auto publish = [&](int s, const double (&Dn)[4], F2 f0, F2 f1, const Raw &r) {
+        SD[s][2 * ty + 1][tx] = F2{Dn[0], Dn[1]};
+        SD[s][2 * ty + 2][tx] = F2{Dn[2], Dn[3]};
+        SF[s][2 * ty + 1][tx] = f0;
+        if (RHO)
+            SF[s][2 * ty + 2][tx] = f1;
+        if (beyond) {
+            SD[s][lb][tx] =
+                F2{dcast(static_cast<double>(r.zb.x), FIRST ? 0.0 : static_cast<double>(r.db.x)),
+                   dcast(static_cast<double>(r.zb.y), FIRST ? 0.0 : static_cast<double>(r.db.y))};
+            SF[s][lb][tx] = r.fb;
+        }
+        if (edge)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                ED[s][2 * ty + h][le] = dcast(static_cast<double>(r.ze[h]),
+                                              FIRST ? 0.0 : static_cast<double>(r.de[h]));
+                EF[s][2 * ty + h][le] = r.fe[h];
+            }
+    };
+    F2 by0{}, by1{}, byn0{}, byn1{};
+    {
+        Raw a{}, c{};
+        D skip[4];
+        load(pm, false, a);
+        load(pc0, true, c);
+        if (!RHO) {
+            by0 = ld2d(by, pc0, o0);
+            by1 = ld2d(by, pc0, o1);
+        }
+        own(a, Dm, skip);
+        own(c, Dc, Oc);
+        Rc[0] = c.f0.x;
+        Rc[1] = c.f0.y;
+        Rc[2] = c.f1.x;
+        Rc[3] = c.f1.y;
+        if (RHO) {
+            ZL[0] = 2.0 / (a.f0.x + Rc[0]);
+            ZL[1] = 2.0 / (a.f0.y + Rc[1]);
+            ZL[2] = 2.0 / (a.f1.x + Rc[2]);
+            ZL[3] = 2.0 / (a.f1.y + Rc[3]);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                ZL[t] = Rc[t];
+        }
+        publish(k0 & 1, Dc, RHO ? c.f0 : by0, c.f1, c);
+    }
+    __syncthreads();
+    for (int k = k0; k < ke; ++k) {
+        const int s = k & 1;
+        const size_t pl = (size_t)k * sz;
+        const size_t pp = (size_t)(k == d.nz - 1 ? 0 : k + 1) * sz;
+        const bool more = k + 1 < ke;
+        // the next plane's loads fly while this plane's x and y terms are formed
+        Raw n{};
+        load(pp, more, n);
+        if (!RHO && more) {
+            byn0 = ld2d(by, pp, o0);
+            byn1 = ld2d(by, pp, o1);
+        }
+        F2 bx0{}, bx1{};
+        if (!RHO) {
+            bx0 = ld2d(bx, pl, o0);
+            bx1 = ld2d(bx, pl, o1);
+        }
+        const F2 ym = SD[s][2 * ty][tx], yp = SD[s][2 * ty + 3][tx];
+        const double De[2] = {ED[s][2 * ty][le], ED[s][2 * ty + 1][le]};
+        const double Fe[2] = {EF[s][2 * ty][le], EF[s][2 * ty + 1][le]};
+        // link coefficients: x faces per row (low, middle, high), y faces
+        // per column (low, middle, high)
+        double fx[2][3], fy[2][3];
+        if (RHO) {
+            const F2 rym = SF[s][2 * ty][tx], ryp = SF[s][2 * ty + 3][tx];
+            fx[0][0] = 2.0 / (from_left(Rc[1], Fe[0]) + Rc[0]);
+            fx[0][1] = 2.0 / (Rc[0] + Rc[1]);
+            fx[0][2] = 2.0 / (Rc[1] + from_right(Rc[0], Fe[0]));
+            fx[1][0] = 2.0 / (from_left(Rc[3], Fe[1]) + Rc[2]);
+            fx[1][1] = 2.0 / (Rc[2] + Rc[3]);
+            fx[1][2] = 2.0 / (Rc[3] + from_right(Rc[2], Fe[1]));
+            fy[0][0] = 2.0 / (rym.x + Rc[0]);
+            fy[0][1] = 2.0 / (Rc[0] + Rc[2]);
+            fy[0][2] = 2.0 / (Rc[2] + ryp.x);
+            fy[1][0] = 2.0 / (rym.y + Rc[1]);
+            fy[1][1] = 2.0 / (Rc[1] + Rc[3]);
+            fy[1][2] = 2.0 / (Rc[3] + ryp.y);
+        } else {
+            const F2 byp = SF[s][2 * ty + 3][tx];
+            fx[0][0] = bx0.x;
+            fx[0][1] = bx0.y;
+            fx[0][2] = from_right(bx0.x, Fe[0]);
+            fx[1][0] = bx1.x;
+            fx[1][1] = bx1.y;
+            fx[1][2] = from_right(bx1.x, Fe[1]);
+            fy[0][0] = by0.x;
+            fy[0][1] = by1.x;
+            fy[0][2] = byp.x;
+            fy[1][0] = by0.y;
+            fy[1][1] = by1.y;
+            fy[1][2] = byp.y;
+        }
+        // per cell: x column cx, row ry; neighbours in x and y
+        const double nxm[4] = {from_left(Dc[1], De[0]), Dc[0], from_left(Dc[3], De[1]), Dc[2]};
+        const double nxp[4] = {Dc[1], from_right(Dc[0], De[0]), Dc[3], from_right(Dc[2], De[1])};
+        const double nym[4] = {ym.x, ym.y, Dc[0], Dc[1]};
+        const double nyp[4] = {Dc[2], Dc[3], yp.x, yp.y};
+        double f[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int cx = c & 1, ry = c >> 1;
+            const double Lxl = (cx == 0 && wxl) ? 0.0 : fx[ry][cx];
+            const double Lxh = (cx == 1 && wxh) ? 0.0 : fx[ry][cx + 1];
+            const double Lyl = (ry == 0 && wyl) ? 0.0 : fy[cx][ry];
+            const double Lyh = (ry == 1 && wyh) ? 0.0 : fy[cx][ry + 1];
+            const double dc = Dc[c];
+            f[c] = Lxh * (nxp[c] - dc) - Lxl * (dc - nxm[c]) + Lyh * (nyp[c] - dc) -
+                   Lyl * (dc - nym[c]);
+        }
+        // (kept below the terms above, whose registers they take)
+        __builtin_amdgcn_sched_barrier(0);
+        D2 ea{}, eb{};
+        F2 va{}, vb{};
+        if (MODE == DIR_TWO && act) {
+            // D_{k-2} is what dnew holds until the stores below
+            ea = ld_once<true>(reinterpret_cast<const D2 *>(at(dnew, pl, o0)));
+            eb = ld_once<true>(reinterpret_cast<const D2 *>(at(dnew, pl, o1)));
+            va = ld_once<true>(reinterpret_cast<const F2 *>(at(x, pl, o0)));
+            vb = ld_once<true>(reinterpret_cast<const F2 *>(at(x, pl, o1)));
+        }
+        // the next plane
+        double Dp[4];
+        D Op[4];
+        own(n, Dp, Op);
+        const double Rp[4] = {n.f0.x, n.f0.y, n.f1.x, n.f1.y};
+        double zh[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            zh[c] = RHO ? 2.0 / (Rc[c] + Rp[c]) : Rp[c];
+        const bool wzl = bc.z && k == 0, wzh = bc.z && k == d.nz - 1;
+        double qq[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double Lzl = wzl ? 0.0 : ZL[c];
+            const double Lzh = wzh ? 0.0 : zh[c];
+            qq[c] = ih2 * (f[c] + Lzh * (Dp[c] - Dc[c]) - Lzl * (Dc[c] - Dm[c]));
+            if (sg)
+                qq[c] -= at(sg, pl, c >> 1 ? o1 : o0)[c & 1] * Dc[c];
+        }
+        if (act) {
+            if (MODE == DIR_TWO) {
+                va.x = (va.x + aprev * static_cast<double>(ea.x)) + aold * static_cast<double>(Oc[0]);
+                va.y = (va.y + aprev * static_cast<double>(ea.y)) + aold * static_cast<double>(Oc[1]);
+                vb.x = (vb.x + aprev * static_cast<double>(eb.x)) + aold * static_cast<double>(Oc[2]);
+                vb.y = (vb.y + aprev * static_cast<double>(eb.y)) + aold * static_cast<double>(Oc[3]);
+                st_once<true>(reinterpret_cast<F2 *>(at(x, pl, o0)), va);
+                st_once<true>(reinterpret_cast<F2 *>(at(x, pl, o1)), vb);
+            }
+            st_once<true>(reinterpret_cast<D2 *>(at(dnew, pl, o0)),
+                        D2{static_cast<D>(Dc[0]), static_cast<D>(Dc[1])});
+            st_once<true>(reinterpret_cast<D2 *>(at(dnew, pl, o1)),
+                        D2{static_cast<D>(Dc[2]), static_cast<D>(Dc[3])});
+            st_once<true>(reinterpret_cast<F2 *>(at(q, pl, o0)), F2{qq[0], qq[1]});
+            st_once<true>(reinterpret_cast<F2 *>(at(q, pl, o1)), F2{qq[2], qq[3]});
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                v[0] += Dc[c] * qq[c];
+                if (!FIRST)
+                    v[1] += static_cast<double>(Oc[c]) * qq[c];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            ZL[c] = zh[c];
+            Dm[c] = Dc[c];
+            Dc[c] = Dp[c];
+            Rc[c] = Rp[c];
+            if (!FIRST)
+                Oc[c] = Op[c];
+        }
+        if (more) {
+            by0 = byn0;
+            by1 = byn1;
+            publish(s ^ 1, Dc, RHO ? n.f0 : by0, n.f1, n);
+            __syncthreads();
         }
     }
     block_partials<2>(v, sm, part, pstride);
@@ -2584,7 +2923,10 @@ void launch_dot_rz(Dims d, const double *r, const T *z, double *part, hipStream_
 
 
 // 2 x 2 cells per thread where the grid and the iterate allow pairs
-bool dir_quad(Dims d, const double *x) { return d.nx % 2 == 0 && d.ny % 2 == 0 && ((uintptr_t)x & 15) == 0; }
+bool dir_quad(Dims d, const double *x)
+{
+    return d.nx % 2 == 0 && d.ny % 2 == 0 && ((uintptr_t)x & 15) == 0;
+}
 
 template <typename T>
 dim3 dir_grid(Dims d, const double *x)
@@ -2608,19 +2950,28 @@ int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const do
     using D = typename DirT<T>::type;
     const bool quad = dir_quad(d, x);
     const dim3 g = dir_grid<T>(d, x);
+    // its offsets within a plane are 32-bit byte offsets
+    const bool rows = quad && streams(d) && (size_t)d.nx * d.ny < (size_t)1 << 29;
     auto go = [&](auto kern) {
         PP_LAUNCH(kern, g, kBlock, 0, s, d, bc, bx, by, bz, rho, z, dold, dnew, q, x, sg,
                   scal, ih2, part, pstride, in);
     };
-    auto by_mode = [&](auto r, auto nt) {
-        constexpr bool RH = decltype(r)::value, NT = decltype(nt)::value;
-        if (quad) {
+    auto by_mode = [&](auto r) {
+        constexpr bool RH = decltype(r)::value;
+        if (rows) {
             if (mode == DIR_FIRST)
-                go(k_dir_apply2<T, D, DIR_FIRST, RH, NT>);
+                go(k_dir_rows<T, D, DIR_FIRST, RH>);
             else if (mode == DIR_HOLD)
-                go(k_dir_apply2<T, D, DIR_HOLD, RH, NT>);
+                go(k_dir_rows<T, D, DIR_HOLD, RH>);
             else
-                go(k_dir_apply2<T, D, DIR_TWO, RH, NT>);
+                go(k_dir_rows<T, D, DIR_TWO, RH>);
+        } else if (quad) {
+            if (mode == DIR_FIRST)
+                go(k_dir_apply2<T, D, DIR_FIRST, RH>);
+            else if (mode == DIR_HOLD)
+                go(k_dir_apply2<T, D, DIR_HOLD, RH>);
+            else
+                go(k_dir_apply2<T, D, DIR_TWO, RH>);
         } else {
             if (mode == DIR_FIRST)
                 go(k_dir_apply<T, D, DIR_FIRST, RH>);
@@ -2630,16 +2981,10 @@ int launch_dir_apply(Dims d, Bc bc, const double *bx, const double *by, const do
                 go(k_dir_apply<T, D, DIR_TWO, RH>);
         }
     };
-    auto by_size = [&](auto r) {
-        if (quad && streams(d))
-            by_mode(r, std::true_type{});
-        else
-            by_mode(r, std::false_type{});
-    };
     if (rho)
-        by_size(std::true_type{});
+        by_mode(std::true_type{});
     else
-        by_size(std::false_type{});
+        by_mode(std::false_type{});
     return (int)grid_blocks(g);
 }
 

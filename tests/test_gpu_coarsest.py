@@ -227,9 +227,10 @@ def test_two_sweep_pass_beyond_2_gib(S, zero):
 
 
 # (nx, ny, nz): one workgroup, odd sizes (a cell per thread), 2 x 2 cells, more
-# partial sums than threads, and a level whose residual update leaves its sums
-# to a kernel of their own
-SOLVES = [(4, 4, 4), (9, 11, 9), (24, 20, 28), (96, 80, 64), (256, 192, 128)]
+# partial sums than threads, and two grids of the direction pass that exchanges
+# rows: one whose residual update leaves its sums to a kernel of their own, one
+# whose last block along x has 8 lanes
+SOLVES = [(4, 4, 4), (9, 11, 9), (24, 20, 28), (96, 80, 64), (256, 192, 128), (272, 176, 80)]
 
 
 @pytest.mark.parametrize("n", SOLVES)
@@ -250,9 +251,13 @@ def test_solve_scalars(S, n, precision):
         p = sol.solve(b, tol=1e-9).clone()
         again = sol.solve(b, tol=1e-9)
         rel = float((b - sol.apply(p)).norm() / b.norm())
-    print(n, precision, "rel %.3e" % rel, flush=True)
+        # link coefficients formed from densities
+        sol.update_density(0.1 + torch.rand(shape, generator=g, dtype=torch.float64).cuda())
+        p2 = sol.solve(b, tol=1e-9)
+        rel2 = float((b - sol.apply(p2)).norm() / b.norm())
+    print(n, precision, "rel %.3e %.3e" % (rel, rel2), flush=True)
     assert torch.equal(p, again)
-    assert rel <= 1e-9 * (1 + 1e-3) + 1e-12
+    assert max(rel, rel2) <= 1e-9 * (1 + 1e-3) + 1e-12
 
 
 @pytest.mark.parametrize("n", [(192, 128, 128), (256, 160, 80)])
