@@ -13,6 +13,7 @@
 
 #include "pp_device.h"
 #include "pp_internal.h"
+#include "pp_planes.h"
 
 namespace pp {
 
@@ -557,13 +558,6 @@ constexpr int GLR = GRY + 2;              // LDS rows: one beyond on each side
 constexpr unsigned FLAT_NONE = 0x7ffffff0u;
 inline bool fused2_flat(Dims d, size_t word) { return cells(d) * word <= FLAT_NONE; }
 
-// Planes of loads in flight beyond k+1: three for FP32; one for FP16 (whose
-// registers then allow two workgroups per CU) and for FP64 (two spill).
-template <typename T>
-struct Fused2Depth {
-    static constexpr int value = sizeof(T) == 4 ? 3 : 1;
-};
-
 // what phase A (B) computed for a cell, for phase C (D) two steps later
 template <typename C>
 struct GsLag {
@@ -607,8 +601,8 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
     constexpr bool EXACT = std::is_same<T, _Float16>::value;
     // The loop is unrolled by the buffer count FNB, a multiple of both slot
     // periods (2 and NRED), so every LDS slot index is a compile-time constant.
-    constexpr int FPD = Fused2Depth<T>::value;
-    constexpr int FNB = FPD + 3;
+    constexpr int FPD = two_sweep_depth(sizeof(T));
+    constexpr int FNB = two_sweep_unroll(sizeof(T));
     constexpr int NRED = FNB % 3 == 0 ? 3 : (FNB % 4 == 0 ? 4 : 5);
     static_assert(FNB % 2 == 0 && FNB % NRED == 0, "slot periods");
     static_assert(!DOT || (!ZERO && !SIG), "the dot product rides on regular passes");
@@ -673,14 +667,13 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
     const int li = (rl + 4) * GLW + pl + 1;          // LDS entry of the pair
     const int lio = li + (dn_row ? -GLW : GLW);      // ... of the row beyond
 
-    // plane q: its wrapped index, and whether it exists (walls end the grid);
-    // selects rather than branches (q is within four planes of the grid)
-    auto plane = [&](int q, int &qw) -> bool {
-        const bool lo = q < 0, hi = q >= d.nz;
-        qw = lo ? q + d.nz : (hi ? q - d.nz : q);
-        const bool ok = !(bc.z && (lo || hi));
-        qw = ok ? qw : 0;
-        return ok;
+    // plane q: its wrapped index, and whether it is read.  Planes past the last
+    // one needed lie outside the array where the grid does not have them: the
+    // range check of a whole-array resource answers those with zeros, resources
+    // of single planes must not be made for them.  (Bounding both forms costs the
+    // FP32 cases 2%: 161 -> 177 registers.)
+    auto plane = [&](int q, int &qw) {
+        return march_plane<!FLAT>(q, d.nz, bc.z, two_sweep_last_plane(k1), qw);
     };
     const unsigned abytes = FLAT ? pbytes * (unsigned)d.nz : 0u;
     const auto fe = plane_rsrc(ein, abytes), fr = plane_rsrc(r, abytes),
@@ -780,7 +773,7 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
     // LDS slots are counted from the first plane of the march, kb = k0 - 3:
     // plane k's inputs sit in slot (k - kb) mod 2, its phase-A values in slot
     // (k - kb) mod NRED; u is the unrolled step index, (k - kb) mod FNB
-    const int kb = k0 - 3;
+    const int kb = two_sweep_first(k0);
     const int p0 = (c0 + j + kb) & 1;
     // the next pair in x of a cell at offset p0 of its pair, and at the other
     const int ladj[2] = {li + (p0 ? 1 : -1), li + (p0 ? -1 : 1)};
@@ -922,7 +915,7 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
     if constexpr (WHOLE) {
         // whole blocks of FNB steps, the last up to FNB - 1 steps past k1 + 2
         // (they store nothing), as in the single sweep
-        for (int k = kb; k <= k1 + 2; k += FNB) {
+        for (int k = kb; k <= two_sweep_end(k1); k += FNB) {
 #pragma unroll
             for (int u = 0; u < FNB; ++u)
                 step(k + u, u, buf[u % FNB], buf[(u + 1) % FNB], buf[(u + 2) % FNB],
@@ -934,7 +927,7 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
             for (int u = 0; u < FNB; ++u) {
                 step(k, u, buf[u % FNB], buf[(u + 1) % FNB], buf[(u + 2) % FNB],
                      buf[(u + FNB - 1) % FNB]);
-                if (++k > k1 + 2) {
+                if (++k > two_sweep_end(k1)) {
                     more = 0;
                     break;
                 }

@@ -231,8 +231,8 @@ template <typename T>
 void launch_rbgs_fused(Dims d, Bc bc, const T *bx, const T *by, const T *bz, const T *r,
                        const T *ein, T *eout, const T *sg, double h2, double omega,
                        int first_colour, bool zero, hipStream_t s);
-// Two sweeps in one pass, out of place, ein and eout distinct; needs nz >= 8
-// (the chunks read four planes beyond their ends).
+// Two sweeps in one pass, out of place, ein and eout distinct; sides of at least
+// 8 cells (a chunk reads four planes beyond its ends, a tile wraps once).
 template <typename T>
 void prepare_fused2();
 // With part given, an FP32 or FP64 regular pass without sigma also writes the partial
