@@ -752,8 +752,8 @@ void *fused_sweeps(pp_ctx *c, LevelBuf &v, int l, int nu, void *cur, int first_c
             // the last pass may also form the outer loop's dot product
             const bool last = sw + 2 == nu;
             const int np = launch_rbgs_fused2<T>(
-                v.d, c->bc, b0, b1, b2, (const T *)v.r, (const T *)cur, (T *)out, (const T *)v.s, h2,
-                c->opts.omega, first_colour, zero, s, (last && dot) ? c->part : nullptr,
+                v.d, c->bc, b0, b1, b2, (const T *)v.r, (const T *)cur, (T *)out, (const T *)v.s, c->gen,
+                h2, c->opts.omega, first_colour, zero, s, (last && dot) ? c->part : nullptr,
                 3 * (long long)c->pstride);
             if (last && np > 0)
                 c->dot_np = np;
@@ -2055,7 +2055,7 @@ int pp_k_smooth2_fused_f32(const pp_grid *grid, const float *bx, const float *by
         return fail(PP_EINVAL, "pp_k_smooth2_fused_f32: every cell count must be >= 8");
     if (!fused_plane_fits(to_dims(grid), sizeof(float)))
         return fail(PP_EINVAL, "pp_k_smooth2_fused_f32: an x-y plane must stay below 2^31 bytes");
-    launch_rbgs_fused2<float>(to_dims(grid), to_bc(grid), bx, by, bz, r, e_in, e_out, nullptr,
+    launch_rbgs_fused2<float>(to_dims(grid), to_bc(grid), bx, by, bz, r, e_in, e_out, nullptr, false,
                               grid->h * grid->h, omega, first_colour, zero_init != 0,
                               (hipStream_t)hip_stream);
     return check_launch("pp_k_smooth2_fused_f32");
@@ -2072,7 +2072,7 @@ int pp_k_smooth2_fused_dot_f32(const pp_grid *grid, const float *bx, const float
     double *part = nullptr;
     PP_HIP(hipMalloc((void **)&part, sizeof(double) * nparts_max));
     hipStream_t s = (hipStream_t)hip_stream;
-    const int np = launch_rbgs_fused2<float>(d, to_bc(grid), bx, by, bz, r, e_in, e_out, nullptr,
+    const int np = launch_rbgs_fused2<float>(d, to_bc(grid), bx, by, bz, r, e_in, e_out, nullptr, false,
                                              grid->h * grid->h, omega, first_colour, false, s,
                                              part, (long long)nparts_max);
     int rc = PP_OK;
@@ -2106,7 +2106,7 @@ int pp_k_smooth2_fused_dot_f32_noalloc(const pp_grid *grid, const float *bx, con
     // the launch writes at most nparts_max partial sums (checked above against
     // the array size)
     const int np = launch_rbgs_fused2<float>(to_dims(grid), to_bc(grid), bx, by, bz, r, e_in,
-                                             e_out, nullptr, grid->h * grid->h, omega,
+                                             e_out, nullptr, false, grid->h * grid->h, omega,
                                              first_colour, false, s, part, (long long)nparts_max);
     PP_TRY(check_launch("pp_k_smooth2_fused_dot_f32_noalloc"));
     if (np <= 0 || (size_t)np > nparts_max)

@@ -586,10 +586,13 @@ __device__ __forceinline__ C rounded_product(C a, C b)
 // in FP64 (the outer iteration's residual against the preconditioned one,
 // both in units of the V-cycle's scale); part[workgroup].  The values of r that
 // phases C and D already carry supply it (as h^2 r), so nothing more is loaded.
+// CLOSED: the operator may have closed links, so a cell may be excluded (the
+// pressure operator has none).  Such a cell holds what the prolongation left
+// there and gets 0, as from the other smoothers.
 // FP16 storage sums x, y, z faces low before high (EXACT): its iterates
 // repeat only with every FP32 rounding, so which products are fused is spelt
 // out below.
-template <typename T, bool ZERO, bool SIG, bool DOT, bool WHOLE, bool FLAT>
+template <typename T, bool ZERO, bool SIG, bool CLOSED, bool DOT, bool WHOLE, bool FLAT>
 __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused2(
     Dims d, Bc bc, const T *__restrict__ bx, const T *__restrict__ by, const T *__restrict__ bz,
     const T *__restrict__ r, const T *__restrict__ ein, T *__restrict__ eout,
@@ -825,7 +828,7 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
         C red = fma(-h2, ra, s) * inva;
         if (!ZERO) {
             red = fma(om1, pick(o, pc.e), red);
-            if (SIG)
+            if (SIG || CLOSED)
                 red = inva == C(0) ? C(0) : red;   // an excluded cell stays 0
         }
         if (act)
@@ -859,7 +862,7 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
                 invb;
         if (!ZERO) {
             blk = fma(om1, pick(o, pm.e), blk);
-            if (SIG)
+            if (SIG || CLOSED)
                 blk = invb == C(0) ? C(0) : blk;
         }
         if (act)
@@ -952,7 +955,7 @@ __global__ __launch_bounds__(GTHREADS, sizeof(T) == 2 ? 4 : 2) void k_rbgs_fused
     }
 }
 
-template <typename T, bool ZERO, bool SIG, bool DOT>
+template <typename T, bool ZERO, bool SIG, bool CLOSED, bool DOT>
 static long long fused2_slots()
 {
     static long long cached[64] = {0};
@@ -963,7 +966,7 @@ static long long fused2_slots()
     if (cached[dev] == 0) {
         int per_cu = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, k_rbgs_fused2<T, ZERO, SIG, DOT, !std::is_same<T, float>::value, true>,
+                &per_cu, k_rbgs_fused2<T, ZERO, SIG, CLOSED, DOT, !std::is_same<T, float>::value, true>,
                 GTHREADS, 0) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
@@ -975,88 +978,81 @@ static long long fused2_slots()
     return cached[dev];
 }
 
+// FP16 storage keeps the excluded cells of an operator without a diagonal term as
+// they were prolonged: its iterates repeat only with them.
+template <typename T>
+constexpr bool zeroes_excluded = !std::is_same<T, _Float16>::value;
+
 template <typename T>
 void prepare_fused2()
 {
-    (void)fused2_slots<T, true, false, false>();
-    (void)fused2_slots<T, false, false, false>();
-    (void)fused2_slots<T, true, true, false>();
-    (void)fused2_slots<T, false, true, false>();
-    if constexpr (!std::is_same<T, _Float16>::value)
-        (void)fused2_slots<T, false, false, true>();
+    constexpr bool ZX = zeroes_excluded<T>, MAY = !std::is_same<T, _Float16>::value;
+    (void)fused2_slots<T, true, false, false, false>();
+    (void)fused2_slots<T, false, false, false, false>();
+    (void)fused2_slots<T, false, false, ZX, false>();
+    (void)fused2_slots<T, true, true, false, false>();
+    (void)fused2_slots<T, false, true, false, false>();
+    if constexpr (MAY) {
+        (void)fused2_slots<T, false, false, false, true>();
+        (void)fused2_slots<T, false, false, ZX, true>();
+    }
 }
 
 template <typename T>
 int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, const T *r,
-                       const T *ein, T *eout, const T *sg, double h2, double omega,
+                       const T *ein, T *eout, const T *sg, bool closed, double h2, double omega,
                        int first_colour, bool zero, hipStream_t s, double *part, long long max_parts)
 {
     using C = typename Acc<T>::type;
     // the first tile of a row with walls owns four cells more (see the kernel)
     const unsigned tx = bc.x ? (d.nx > GTX + 4 ? (d.nx - 4 + GTX - 1) / GTX : 1) : (d.nx + GTX - 1) / GTX;
     const unsigned ty = (d.ny + GTY - 1) / GTY;
-    // the fused dot product: regular passes without a diagonal term (FP16
-    // storage keeps the sum of its own kernel)
-    constexpr bool MAY = !std::is_same<T, _Float16>::value;
-    const bool dot = MAY && part && !zero && !sg;
-    long long slots;
-    if (dot)
-        slots = fused2_slots<T, false, false, MAY>();
-    else
-        slots = sg ? (zero ? fused2_slots<T, true, true, false>()
-                           : fused2_slots<T, false, true, false>())
-                   : (zero ? fused2_slots<T, true, false, false>()
-                           : fused2_slots<T, false, false, false>());
-    // chunks of at least two planes; a pass that forms the dot product writes a
-    // partial sum per workgroup, at most max_parts of them
     const long long tiles = (long long)tx * ty;
-    const int kz = chunk_planes(d.nz, tiles, slots, 6, 2, dot ? max_parts / tiles : d.nz);
-    const unsigned tz = (d.nz + kz - 1) / kz;
-    const dim3 grid(tx * ty, tz);
     // A chunk marches kz + 6 steps.  FP32 runs short ones with an exit after
     // every step (whole blocks of six would march 12 steps for 8); FP16 and FP64
     // always run whole blocks, of four: the other form's registers spill.
     constexpr bool SHORT = std::is_same<T, float>::value;
-    const bool whole = !SHORT || kz + 6 >= WHOLE_MIN_STEPS;
-    auto go = [&](auto kern) {
-        PP_LAUNCH(kern, grid, dim3(GTHREADS), 0, s, d, bc, bx, by, bz, r, ein, eout, sg, (C)h2,
-                  (C)omega, first_colour, kz, tx, ty, part);
-    };
-    auto form = [&](auto z, auto g, auto dt) {
-        constexpr bool Z = decltype(z)::value, G = decltype(g)::value, DT = decltype(dt)::value;
+    auto form = [&](auto z, auto g, auto x, auto dt) -> int {
+        constexpr bool Z = decltype(z)::value, G = decltype(g)::value, X = decltype(x)::value,
+                       DT = decltype(dt)::value;
+        // chunks of at least two planes; a pass that forms the dot product writes a
+        // partial sum per workgroup, at most max_parts of them
+        const int kz = chunk_planes(d.nz, tiles, fused2_slots<T, Z, G, X, DT>(), 6, 2,
+                                    DT ? max_parts / tiles : d.nz);
+        const dim3 grid(tx * ty, (d.nz + kz - 1) / kz);
+        const bool whole = !SHORT || kz + 6 >= WHOLE_MIN_STEPS;
+        auto go = [&](auto kern) {
+            PP_LAUNCH(kern, grid, dim3(GTHREADS), 0, s, d, bc, bx, by, bz, r, ein, eout, sg, (C)h2,
+                      (C)omega, first_colour, kz, tx, ty, part);
+        };
         if (!fused2_flat(d, sizeof(T)))
-            go(k_rbgs_fused2<T, Z, G, DT, true, false>);
+            go(k_rbgs_fused2<T, Z, G, X, DT, true, false>);
         else if (whole)
-            go(k_rbgs_fused2<T, Z, G, DT, true, true>);
+            go(k_rbgs_fused2<T, Z, G, X, DT, true, true>);
         else
-            go(k_rbgs_fused2<T, Z, G, DT, !SHORT, true>);
+            go(k_rbgs_fused2<T, Z, G, X, DT, !SHORT, true>);
+        return DT ? (int)(grid.x * grid.y) : 0;
     };
     constexpr std::true_type Y{};
     constexpr std::false_type N{};
-    if (dot) {
-        if constexpr (MAY)
-            form(N, N, Y);
-        return (int)(grid.x * grid.y);
-    }
-    if (sg) {
-        if (zero)
-            form(Y, Y, N);
-        else
-            form(N, Y, N);
-    } else {
-        if (zero)
-            form(Y, N, N);
-        else
-            form(N, N, N);
-    }
-    return 0;
+    if (sg)
+        return zero ? form(Y, Y, N, N) : form(N, Y, N, N);
+    if (zero)
+        return form(Y, N, N, N);
+    constexpr std::bool_constant<zeroes_excluded<T>> ZX{};
+    // the fused dot product: regular passes without a diagonal term (FP16
+    // storage keeps the sum of its own kernel)
+    if constexpr (!std::is_same<T, _Float16>::value)
+        if (part)
+            return closed ? form(N, N, ZX, Y) : form(N, N, N, Y);
+    return closed ? form(N, N, ZX, N) : form(N, N, N, N);
 }
 
 #define PP_INSTANTIATE_FUSED2(T)                                                                 \
     template void prepare_fused2<T>();                                                          \
     template int launch_rbgs_fused2<T>(Dims, Bc, const T *, const T *, const T *, const T *,    \
-                                       const T *, T *, const T *, double, double, int, bool,     \
-                                       hipStream_t, double *, long long);
+                                       const T *, T *, const T *, bool, double, double, int,     \
+                                       bool, hipStream_t, double *, long long);
 
 PP_INSTANTIATE_FUSED2(double)
 PP_INSTANTIATE_FUSED2(float)

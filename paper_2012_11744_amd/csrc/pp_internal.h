@@ -238,10 +238,11 @@ void prepare_fused2();
 // With part given, an FP32 or FP64 regular pass without sigma also writes the partial
 // sums of r . e_out (its own right-hand side against its output, products in
 // FP64), one per workgroup, and returns their number (at most max_parts, which
-// must be at least the number of its x-y tiles); otherwise returns 0.
+// must be at least the number of its x-y tiles); otherwise returns 0.  closed:
+// the operator may have closed links (cells without any are excluded).
 template <typename T>
 int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, const T *r,
-                       const T *ein, T *eout, const T *sg, double h2, double omega,
+                       const T *ein, T *eout, const T *sg, bool closed, double h2, double omega,
                        int first_colour, bool zero, hipStream_t s, double *part = nullptr,
                        long long max_parts = 0);
 inline bool fused2_fits(Dims d) { return d.nz >= 8 && d.nx >= 8 && d.ny >= 8; }
