@@ -495,7 +495,9 @@ int await_pinv(pp_ctx *c)
 // the verdict on the rebuilt pseudo-inverse, from scalars published behind it
 int pinv_verdict(pp_ctx *c, const double *scal)
 {
-    if (c->pinv_unchecked && scal[S_PINVBAD] != 0.0)
+    if (c->pinv_unchecked && scal[S_PINVBAD] == PINV_ZERO)
+        return fail(PP_EINVAL, "coarsest operator is zero");
+    if (c->pinv_unchecked && scal[S_PINVBAD] != PINV_GOOD)
         return fail(PP_EINVAL, "coarsest operator is not definite on mean-zero fields "
                                "(disconnected domain?)");
     c->pinv_unchecked = false;

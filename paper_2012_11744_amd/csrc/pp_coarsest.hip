@@ -49,7 +49,7 @@ struct PinvArgs {
     double *out;                         // np x np work matrix
     double *meta;                        // per cell: -A_cc if active, else 0; then M_COUNT scalars
     double *pinv;                        // n x n
-    double *bad;                         // 1 where a pivot is not a positive number, else 0
+    double *bad;                         // PINV_GOOD, PINV_BAD or PINV_ZERO
 };
 
 // scalars behind the cells' entries of meta
@@ -111,9 +111,11 @@ __device__ __forceinline__ void reduce2(double &u, double &v, double (*red)[NT /
 }
 
 // s / n, 1 / (s n) and 1 / n over the active cells (0 for a definite operator),
-// by the whole workgroup, and every cell's -A_cc (0 if inactive) to dg
+// whether there are any, by the whole workgroup, and every cell's -A_cc (0 if
+// inactive) to dg
 struct Shift {
     double base, shift, invn;
+    bool any;
 };
 
 template <int NT>
@@ -128,7 +130,7 @@ __device__ __forceinline__ Shift shift_of(const PinvArgs &a, double *dg, double 
     }
     reduce2<true, NT>(s, na, red);
     const bool on = a.singular && na > 0.0;
-    return Shift{on ? s / na : 0.0, on ? 1.0 / (s * na) : 0.0, on ? 1.0 / na : 0.0};
+    return Shift{on ? s / na : 0.0, on ? 1.0 / (s * na) : 0.0, on ? 1.0 / na : 0.0, na > 0.0};
 }
 
 // A row of K = -A + base 1 1^T over the active cells, after the workgroup has
@@ -165,8 +167,10 @@ __global__ __launch_bounds__(FTHREADS) void k_pinv_fill(PinvArgs a)
     if (t < PROWS && r0 + t < a.n) {
         finish_row(row_of(a, r0 + t), r0 + t, sh.base, a.out + (size_t)(r0 + t) * a.np);
         a.meta[r0 + t] = dg[r0 + t];
-        if (r0 + t == 0)
+        if (r0 + t == 0) {
             a.meta[a.n + M_SHIFT] = sh.shift;
+            *a.bad = sh.any ? PINV_GOOD : PINV_ZERO;
+        }
     }
 }
 
@@ -275,6 +279,7 @@ __global__ __launch_bounds__(FTHREADS) void k_pinv_reduce(PinvArgs a)
             a.meta[a.n + M_GAMMA] = gamma;
             a.meta[a.n + M_INVN] = sh.invn;
             a.meta[a.n + M_SUMQ] = sq;
+            *a.bad = sh.any ? PINV_GOOD : PINV_ZERO;
         }
     }
 }
@@ -495,7 +500,7 @@ __global__ __launch_bounds__(PTHREADS) void k_pinv_small(PinvArgs a)
             v[q][p] = Km[tile_row(ti, p) * PLD + tj + 16 * q];
     const bool bad = invert_tile(v, ti, tj, piv);
     if (t == 0)
-        *a.bad = bad ? 1.0 : 0.0;
+        *a.bad = bad ? PINV_BAD : (sh.any ? PINV_GOOD : PINV_ZERO);
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
@@ -547,8 +552,8 @@ __global__ __launch_bounds__(PTHREADS) void k_pinv_step(PinvArgs a)
             Ym[l] = row[o + (size_t)K * PB * a.np + J * PB];
         }
     const bool bad = invert_tile(v, ti, tj, piv);
-    if (I == 0 && J == 0 && t == 0 && (K == 0 || bad))
-        *a.bad = bad ? 1.0 : 0.0;
+    if (I == 0 && J == 0 && t == 0 && bad)
+        *a.bad = PINV_BAD;               // (the fill wrote the verdict before)
     if (I != K || J != K) {
 #pragma unroll
         for (int p = 0; p < 4; ++p)

@@ -190,10 +190,14 @@ enum Slot {
     S_NACT = 14,    // active cells of the general operator
     S_DS = 15,      // V-cycle scale of the latest direction (outer CG)
     S_APREV = 16,   // the previous outer iteration's ALPHA
-    S_PINVBAD = 17, // the coarsest pseudo-inverse met a pivot that is not a positive number
+    S_PINVBAD = 17, // PINV_GOOD, PINV_BAD or PINV_ZERO
     S_RZNEW = 18,   // r . z of the iteration under way
     S_NSLOTS = 19
 };
+
+// the coarsest pseudo-inverse: as it should be; met a pivot that is not a positive
+// number; or no coarsest cell has an open face or a diagonal term
+constexpr double PINV_GOOD = 0.0, PINV_BAD = 1.0, PINV_ZERO = 2.0;
 
 enum FinalizeOp {
     OP_STORE = 0,   // scal[slot] = sum0
@@ -271,7 +275,8 @@ void launch_prolong_weights(Dims d, Bc bc, const double *bx, const double *by, c
 // the pseudo-inverse of the coarsest level's operator (n = cells(d) <= 1024)
 // from its FP64 coefficients and sigma (or null); singular: the constants on
 // the active cells are its null space; work: pinv_work_doubles(n) doubles;
-// *bad = 1 where the operator is not definite (off that null space), else 0
+// *bad: PINV_BAD where the operator is not definite (off that null space),
+// PINV_ZERO where it is zero, else PINV_GOOD
 size_t pinv_work_doubles(int n);
 void launch_pinv(Dims d, Bc bc, double h, const double *const b[3], const double *sg,
                  bool singular, double *work, double *pinv, double *bad, hipStream_t s);
