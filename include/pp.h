@@ -177,7 +177,9 @@ int pp_setup(const pp_grid *grid, const double *beta_x, const double *beta_y,
  *    over the active cells and returns p with zero mean over them.  The
  *    active cells must then be connected (the caller checks this, as the
  *    paper leaves it to a separate percolation check); otherwise the solve
- *    stalls and returns PP_ENOCONV.  With a positive sigma nothing is removed.
+ *    ends with PP_ENOCONV or PP_EDIVERGED, or with PP_EINVAL where the
+ *    coarsest level's operator cannot be inverted (p is then as it was, 0 on a
+ *    cold start).  With a positive sigma nothing is removed.
  * On a context made here every later call uses A_g: pp_apply returns A_g x;
  * pp_divergence gives closed links no flux; pp_project writes u = 0 on
  * closed links (as on walls); pp_solve_adjoint writes g_beta = 0 on closed

@@ -1192,6 +1192,10 @@ int pcg_loop(pp_ctx *c, Hier &H, double *x, double tol, SolveState &S)
     }
     if (rc == CONVERGED)
         rc = PP_OK;
+    // directions formed with a rejected pseudo-inverse (the first iteration brings
+    // its verdict, before a second is queued) leave the iterate as it was
+    if (c->pinv_unchecked)
+        return rc;
     // the updates of the iterate still pending: the last direction (in dold
     // after the swap), and after an odd last iteration also the one before it
     // (in dnew), whose pass held it
@@ -1338,6 +1342,8 @@ int solve_impl(pp_ctx *c, const double *rhs, double *x, double tol, pp_stats *st
     PP_TRY(true_residual(c, rhs, x, !warm, S, false, nullptr, pcg ? &pre : nullptr));
     int rc = PP_OK;
     bool gauged = false;   // x is gauged and unchanged since
+    if (!(S.nb > 0.0 && S.rel > tol))
+        PP_TRY(check_pinv(c));   // no iteration brings its verdict
     if (!(S.nb > 0.0)) {
         // b = 0 after mean removal: the mean-zero solution is 0
         launch_fill(x, c->N, 0.0, c->stream);
@@ -1382,8 +1388,6 @@ int solve_impl(pp_ctx *c, const double *rhs, double *x, double tol, pp_stats *st
             break;
         }
     }
-    if (S.it == 0)
-        PP_TRY(check_pinv(c));   // no iteration brought its verdict
     if ((rc == PP_OK || rc == PP_ENOCONV) && !gauged)
         PP_TRY(gauge(c, x));
     if (tail_queued)

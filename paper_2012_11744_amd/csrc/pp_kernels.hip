@@ -1811,6 +1811,10 @@ template <typename T>
 __global__ void k_axpy_T(size_t n, const T *__restrict__ e, double *__restrict__ x,
                          const double *__restrict__ scal)
 {
+    // a correction formed with a rejected pseudo-inverse is not added: the host
+    // learns of it with this iteration's scalars
+    if (scal[S_PINVBAD] != PINV_GOOD)
+        return;
     const double s = scal[S_USED];
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
          i += (size_t)gridDim.x * blockDim.x)
