@@ -13,7 +13,6 @@
 
 #include "pp_device.h"
 #include "pp_internal.h"
-#include "pp_planes.h"
 
 namespace pp {
 

@@ -8,6 +8,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "pp_planes.h"
+
 namespace pp {
 
 // Kernel timing without markers: the host driver's timer scope leaves a pair
@@ -39,7 +41,7 @@ constexpr int BLOCK = BX * BY;
 
 struct Dims {
     int nx, ny, nz;
-    // Reductions over this grid keep blocks of 8 planes and with them the order
+    // Reductions over this grid keep blocks of FIXED_PLANES and with them the order
     // of their sums (level 0 of an FP16-storage context).  There a change in the
     // last bit of a scalar, by way of one rounding of the stored direction,
     // reaches the FP16 roundings of the V-cycle and through them every cell: the
@@ -89,23 +91,10 @@ inline dim3 colour_grid(Dims d)
 
 inline size_t grid_blocks(dim3 g) { return (size_t)g.x * g.y * g.z; }
 
-// Kernels that reduce, and the density load, walk several planes per block
-// (fewer partial sums, neighbours from cache), but no more than leave 2048
-// blocks, eight per CU: on a small grid a walk is a chain of memory round
-// trips on a few CUs (32^3 in blocks of 8 planes: 16 blocks, 33 us for the
-// density load, 12 us in blocks of one coarse plane).  A kernel takes its
-// planes per block from its grid (block_planes).
-inline int walk_planes(int nz, size_t xy_blocks, int most)
-{
-    while (most > 1 && xy_blocks * ((nz + most - 1) / most) < 2048)
-        most /= 2;
-    return most;
-}
-
 inline dim3 red_grid(Dims d)
 {
     const unsigned gx = (d.nx + BX - 1) / BX, gy = (d.ny + BY - 1) / BY;
-    const int rz = d.fixed_order ? 8 : walk_planes(d.nz, (size_t)gx * gy, 8);
+    const int rz = d.fixed_order ? FIXED_PLANES : walk_planes(d.nz, (size_t)gx * gy, 8);
     return dim3(gx, gy, (d.nz + rz - 1) / rz);
 }
 
@@ -123,6 +112,7 @@ inline dim3 quad_grid(Dims d, bool wide)
     const unsigned gx = (d.nx / 2 + BX - 1) / BX, gy = (d.ny / 2 + BY - 1) / BY;
     const size_t xy = (size_t)gx * gy;
     int kz = 8;
+    static_assert(FIXED_PLANES == 8, "the chunk of a fixed order");
     if (!d.fixed_order && !(wide && xy * ((d.nz + 7) / 8) >= 256))
         while (kz > 1 && xy * ((d.nz + kz - 1) / kz) < 512)
             kz /= 2;
@@ -162,10 +152,10 @@ inline size_t partials_max(Dims d)
 }
 
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
-// planes per block of a grid whose z extent is ceil(nz / planes)
-__device__ __forceinline__ int block_planes(int nz)
+// planes per block of a grid of one of the rules above
+__device__ __forceinline__ int block_planes(Dims d)
 {
-    return (int)((nz + gridDim.z - 1) / gridDim.z);
+    return planes_of(d.nz, (int)gridDim.z, d.fixed_order != 0);
 }
 #endif
 

@@ -849,7 +849,7 @@ __global__ __launch_bounds__(BLOCK) void k_load_density(Dims fd, Bc bc, const do
         const int xu = (x + 2 == fd.nx) ? 0 : x + 2;
         const int yu = (y + 2 == fd.ny) ? 0 : y + 2, yu3 = (yu + 1 == fd.ny) ? 0 : yu + 1;
         const bool wxu = bc.x && xu == 0, wyu = bc.y && yu == 0;
-        const int kz = block_planes(cd.nz);
+        const int kz = block_planes(cd);
         const int Ke = min(cd.nz, ((int)blockIdx.z + 1) * kz);
         for (int K = blockIdx.z * kz; K < Ke; ++K) {
             const int z = 2 * K;
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(BLOCK) void k_check_rho(Dims d, const double *__res
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const double r = rho[((size_t)k * d.ny + j) * d.nx + i];
@@ -989,7 +989,7 @@ __global__ __launch_bounds__(BLOCK) void k_check_beta(Dims d, Bc bc, const doubl
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
@@ -1013,7 +1013,7 @@ __global__ __launch_bounds__(BLOCK) void k_check_sigma(Dims d, const double *__r
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[2] = {0.0, 0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const double x = sg[((size_t)k * d.ny + j) * d.nx + i];
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(BLOCK) void k_active(Dims d, Bc bc, const double *_
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
@@ -1149,7 +1149,7 @@ __global__ __launch_bounds__(BLOCK) void k_divergence_sum(Dims d, Bc bc,
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
@@ -1292,7 +1292,7 @@ __global__ __launch_bounds__(BLOCK) void k_sum(Dims d, const double *__restrict_
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
@@ -1570,7 +1570,7 @@ __global__ __launch_bounds__(BLOCK) void k_residual(Dims d, Bc bc, const double 
     double v[3] = {0.0, 0.0, 0.0};
     if (i < d.nx && j < d.ny) {
         const double mean = scal[S_MEAN];
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
@@ -1647,7 +1647,7 @@ __global__ __launch_bounds__(BLOCK) void k_residual2(Dims d, Bc bc, const double
             o[3] = c.y;
         };
         // cells 0: (x0, j0), 1: (x0 + 1, j0), 2: (x0, j1), 3: (x0 + 1, j1)
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int k0 = (int)gbz * kz;
         const int ke = min(d.nz, k0 + kz);
         const size_t pm0 = (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz;
@@ -1779,7 +1779,7 @@ __global__ __launch_bounds__(BLOCK) void k_residual_T(Dims d, Bc bc, const doubl
     if (i < d.nx && j < d.ny) {
         const double mean = scal[S_MEAN];
         const double inv = 1.0 / scal[S_NEXT];
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const Nb n = neighbours(d, bc, i, j, k);
@@ -1831,7 +1831,7 @@ __global__ __launch_bounds__(BLOCK) void k_dot_rz(Dims d, const double *__restri
     const int j = blockIdx.y * BY + threadIdx.y;
     double v[1] = {0.0};
     if (i < d.nx && j < d.ny) {
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;
@@ -1902,7 +1902,7 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply(Dims d, Bc bc, const double
         const ptrdiff_t oyp = (j == d.ny - 1) ? -(ptrdiff_t)(d.ny - 1) * d.nx : (ptrdiff_t)d.nx;
         const bool wxl = bc.x && i == 0, wxh = bc.x && i == d.nx - 1;
         const bool wyl = bc.y && j == 0, wyh = bc.y && j == d.ny - 1;
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int k0 = blockIdx.z * kz;
         const int ke = min(d.nz, k0 + kz);
         const size_t cm0 = col + (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz;
@@ -2032,7 +2032,7 @@ __global__ __launch_bounds__(BLOCK) void k_dir_apply2(Dims d, Bc bc, const doubl
             return *reinterpret_cast<const F2 *>(p + c);
         };
         // cells 0: (x0, j0), 1: (x0 + 1, j0), 2: (x0, j1), 3: (x0 + 1, j1)
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int k0 = (int)gbz * kz;
         const int ke = min(d.nz, k0 + kz);
         const size_t pm = (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz, pc0 = (size_t)k0 * sz;
@@ -2313,7 +2313,7 @@ __global__ __launch_bounds__(BLOCK, dir_per_cu(sizeof(D), MODE)) void k_dir_rows
     auto from_left = [](double v, double ev) { return dpp<0x138>(ev, v); };
     auto from_right = [](double v, double ev) { return dpp<0x130>(ev, v); };
     // cells 0: (x0, j0), 1: (x0 + 1, j0), 2: (x0, j1), 3: (x0 + 1, j1)
-    const int kz = block_planes(d.nz);
+    const int kz = block_planes(d);
     const int k0 = (int)gbz * kz;
     const int ke = min(d.nz, k0 + kz);
     const size_t pm = (size_t)(k0 == 0 ? d.nz - 1 : k0 - 1) * sz, pc0 = (size_t)k0 * sz;
@@ -2547,7 +2547,7 @@ __global__ __launch_bounds__(BLOCK) void k_pcg_update(Dims d, const double *__re
     }
     if (i < d.nx && j < d.ny) {
         const double inv = 1.0 / scal[S_NEXT];
-        const int kz = block_planes(d.nz);
+        const int kz = block_planes(d);
         const int ke = min(d.nz, ((int)blockIdx.z + 1) * kz);
         for (int k = blockIdx.z * kz; k < ke; ++k) {
             const size_t c = ((size_t)k * d.ny + j) * d.nx + i;

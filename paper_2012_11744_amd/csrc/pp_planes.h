@@ -3,7 +3,32 @@
 #ifndef PP_PLANES_H
 #define PP_PLANES_H
 
+#include <cstddef>
+
 namespace pp {
+
+// Kernels that reduce, and the density load, walk several planes per block
+// (fewer partial sums, neighbours from cache), but no more than leave 2048
+// blocks, eight per CU: on a small grid a walk is a chain of memory round
+// trips on a few CUs (32^3 in blocks of 8 planes: 16 blocks, 33 us for the
+// density load, 12 us in blocks of one coarse plane).
+constexpr int walk_planes(int nz, std::size_t xy_blocks, int most)
+{
+    while (most > 1 && xy_blocks * ((nz + most - 1) / most) < 2048)
+        most /= 2;
+    return most;
+}
+
+// Planes of a block where the order of the sums must not depend on the grid's size
+constexpr int FIXED_PLANES = 8;
+
+// Planes per block from the grid's z extent ceil(nz / planes): as many in every
+// block but the last, or (fixed) FIXED_PLANES and what is left in the last.
+constexpr int planes_of(int nz, int grid_z, bool fixed)
+{
+    return fixed ? FIXED_PLANES : (nz + grid_z - 1) / grid_z;
+}
+
 
 // Plane q of a march along z: its wrapped index in qw, and whether it is read
 // (walls end the grid; BOUNDED: planes past `last` are not needed).  Selects

@@ -71,3 +71,26 @@ int main()
 }
 ''')
     assert r.returncode == 0, r.stdout
+
+
+def test_planes_per_block(tmp_path):
+    """The blocks along z cover the grid, none of them empty, and where the order of
+    the sums is fixed they hold 8 planes whatever nz is (the last what is left)."""
+    r = run_host(tmp_path, r'''
+int main()
+{
+    for (int nz = 1; nz <= 600; ++nz)
+        for (int most = 1; most <= 8; most *= 2)
+            for (std::size_t xy : {1, 7, 64, 300, 5000}) {
+                const int kz = walk_planes(nz, xy, most), gz = (nz + kz - 1) / kz;
+                const int pl = planes_of(nz, gz, false);
+                if (kz < 1 || kz > most || pl > kz || gz * pl < nz || (gz - 1) * pl >= nz)
+                    return 1;
+                const int g8 = (nz + FIXED_PLANES - 1) / FIXED_PLANES;
+                if (FIXED_PLANES != 8 || planes_of(nz, g8, true) != 8)
+                    return 2;
+            }
+    return 0;
+}
+''')
+    assert r.returncode == 0
