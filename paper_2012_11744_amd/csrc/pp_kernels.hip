@@ -1381,10 +1381,7 @@ __device__ __forceinline__ bool first_thread()
     return (threadIdx.x | threadIdx.y | blockIdx.x | blockIdx.y | blockIdx.z) == 0;
 }
 
-// the direction's coefficient: S_BETA, or from the folded sums of r . z.  No
-// workgroup reads the slots that the first one writes.
-// The value is moved to scalar registers, where one loaded from S_BETA would be:
-// the direction pass is short of vector ones.
+// a value that is the same in every lane, moved to scalar registers
 __device__ __forceinline__ double uniform(double v)
 {
     union {
@@ -1396,6 +1393,10 @@ __device__ __forceinline__ double uniform(double v)
     return u.d;
 }
 
+// The direction's coefficient: S_BETA, or from the folded sums of r . z.  No
+// workgroup reads the slots that the first one writes.  It goes to scalar
+// registers, where one loaded from S_BETA would be: the direction pass is short of
+// vector ones.
 template <bool FIRST>
 __device__ __forceinline__ double direction_beta(const FoldIn &in, double (*sm)[BLOCK / 64],
                                                  const double *__restrict__ scal)
@@ -2540,8 +2541,10 @@ __global__ __launch_bounds__(BLOCK) void k_pcg_update(Dims d, const double *__re
         double f[2];
         fold_sums<2>(in, fsm, f);
         alpha = uniform(next_alpha(f[0], scal));
+        // its inputs, S_ALPHA among them, by the pointer that the slots are stored
+        // through: scal is restrict, loads by it may be moved past the stores
         if (first_thread())
-            set_alpha(alpha, f[0], f[1], scal, [&](int q, double v) { in.scal[q] = v; });
+            set_alpha(alpha, f[0], f[1], in.scal, [&](int q, double v) { in.scal[q] = v; });
     } else {
         alpha = scal[S_ALPHA];
     }
