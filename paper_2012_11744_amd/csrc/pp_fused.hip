@@ -532,16 +532,19 @@ void launch_rbgs_fused(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
 // a chunk of output planes [k0, k1) is marched from k0-3 to k1+2.  Per cell the
 // pass moves the bytes of one sweep.
 //
-// What bounds it (256^3 FP32, one workgroup per CU): the loads of a march with
-// the arithmetic taken out take 121 of its 130 us when a tile's rows start 16
-// bytes before a cache line, whatever the number of planes in flight (1 to 9):
-// a CU holds no more lines on their way than its L1, and a row of 72 cells
-// then touches four lines for 2.25.  Rows therefore start on a line (three);
-// the arithmetic alone takes 80 us.  Measured, regular / zero start: 256^3 FP32
-// 133 / 105 -> 120 / 101 us (512^3 1006 / 784 -> 877 / 730), FP16 storage 95 / 93
-// -> 80 / 85; FP64 in this form, with r.z, 191 / 175, where two single sweeps
-// take 335 / 323 and the dot product 47; at 64^3 FP64 10.6 / 10.1, where a
-// launch per colour takes 8 x 5 for two sweeps on each side.
+// What bounds it (256^3 FP32, one workgroup of 512 threads per CU): mostly its
+// loads.  With the arithmetic taken out a march took 121 of then 130 us, whatever
+// the number of planes in flight (1 to 9), with the loads taken out 80.  An L1 has
+// 73 reads on their way on average (75 in the zero-start pass; the copy kernel, at
+// the rate of HBM, 91, the residual update 80), and waits for them in 44% (53%) of
+// its cycles; the rest is the latency of the plane step.  A row of 72 cells that
+// starts 16 bytes before a cache line touches four lines for 2.25, so rows start
+// on a line (three).  Measured, regular / zero start: 256^3 FP32 133 / 105 ->
+// 120 / 101 us, 112 / 96 since the outer kernels stream past the caches (512^3
+// 1006 / 784 -> 877 / 730), FP16 storage 95 / 93 -> 80 / 85; FP64 in this form,
+// with r.z, 191 / 175, where two single sweeps take 335 / 323 and the dot product
+// 47; at 64^3 FP64 10.6 / 10.1, where a launch per colour takes 8 x 5 for two
+// sweeps on each side.
 // ---------------------------------------------------------------------------
 constexpr int GTX = 64;                   // tile width in cells (32 pairs)
 constexpr int GTY = 8;                    // tile height in rows
@@ -1009,7 +1012,9 @@ int launch_rbgs_fused2(Dims d, Bc bc, const T *bx, const T *by, const T *bz, con
     const long long tiles = (long long)tx * ty;
     // A chunk marches kz + 6 steps.  FP32 runs short ones with an exit after
     // every step (whole blocks of six would march 12 steps for 8); FP16 and FP64
-    // always run whole blocks, of four: the other form's registers spill.
+    // always run whole blocks, of four: the other form's registers spill (of the
+    // whole blocks' only the regular pass with a diagonal term, 6 values in FP64
+    // and 1 in FP16).
     constexpr bool SHORT = std::is_same<T, float>::value;
     auto form = [&](auto z, auto g, auto x, auto dt) -> int {
         constexpr bool Z = decltype(z)::value, G = decltype(g)::value, X = decltype(x)::value,

@@ -357,7 +357,7 @@ void launch_publish(const double *src, double *host, int n, hipStream_t s, doubl
 void launch_finalize(const double *part, size_t pstride, int nparts, int op, int slot,
                      double ncells, int first, double *scal, hipStream_t s,
                      double *host = nullptr, double ticket = 0.0);
-// returns the number of partial sums written (at most grid_blocks(red_grid(d)))
+// returns the number of partial sums written (at most partials_max(d))
 // whether launch_residual (x given) forms the link coefficients from rho
 // rather than reading bx, by, bz: the 2 x 2 kernel on even grids with 16-byte
 // aligned arrays
@@ -418,7 +418,7 @@ inline bool folds(Dims d, size_t blocks, size_t n)
 // workgroups of launch_dir_apply
 template <typename T>
 size_t dir_blocks(Dims d, const double *x);
-// returns the number of partial sums written (at most grid_blocks(red_grid(d)))
+// returns the number of partial sums written (at most partials_max(d))
 // rho non-null: the link coefficients are formed from the cell densities
 // (the plain operator whose coefficients came from them), not read from bx..bz.
 // The iterate's update (mode): DIR_FIRST none (first iteration: no D_old),

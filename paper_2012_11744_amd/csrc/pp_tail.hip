@@ -19,7 +19,7 @@
 //  - the restriction's four x-z sums go through LDS once and become the next
 //    level's right-hand side in registers.
 // Measured with 16^3, 8^3 and 4^3 cells, per V-cycle: 18 us in FP32 arithmetic
-// and 32 us in FP64; 33 and 70 us when every value of a pair came from LDS
+// and 29 to 31 us in FP64; 33 and 70 us when every value of a pair came from LDS
 // (FP64 coefficients from L2), two pairs of one plane a thread, a division a cell.
 #include <hip/hip_runtime.h>
 
@@ -381,8 +381,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail_cycle(TailArgs<T> a)
     quad_place(A, dA, tid);
     quad_place(B, dB, two ? tid : TAIL_CELLS);
     // FP32 arithmetic holds both levels' coefficients throughout, loaded here
-    // at once; FP64's would spill, so each level's are loaded (from L2) when its
-    // turn comes
+    // at once.  FP64's are loaded (from L2) when each level's turn comes; with two
+    // levels in one launch 51 of its values are spilled all the same (188 bytes a
+    // lane), with one (the split phases) none.
     constexpr bool KEEP = sizeof(C) == 4;
     constexpr bool EXACT = exact_order<T>();
     quad_coeffs<C, T>(A, dA, a.bc, a.b[0], a.s[0], om);
