@@ -553,6 +553,20 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_tail_cycle(TailArgs<T> a)
     }
 }
 
+// The coarsest correction in storage, by way of the arithmetic's type as every
+// level's: FP16 is rounded twice, to FP32 and from there (the compiler would make
+// one conversion of the two, and now and then another value).
+template <typename TE>
+__device__ __forceinline__ TE stored(double s)
+{
+    if constexpr (exact_order<TE>()) {
+        float f = static_cast<float>(s);
+        asm("" : "+v"(f));
+        return static_cast<TE>(f);
+    }
+    return static_cast<TE>(s);
+}
+
 // Coarsest level by itself: e = A^+ r in FP64, a wave per row of the
 // (symmetric) pseudo-inverse, four rows per workgroup, so that all of it is
 // in flight at once.  720 cells: 4 us, where one workgroup takes 210.
@@ -572,7 +586,7 @@ __global__ __launch_bounds__(256) void k_coarsest(int n, const double *__restric
     for (int o = 32; o > 0; o >>= 1)
         s += __shfl_xor(s, o, 64);
     if (lane == 0)
-        e[row] = static_cast<TE>(s);
+        e[row] = stored<TE>(s);
 }
 
 template <typename T>
